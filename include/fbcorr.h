@@ -71,6 +71,12 @@ typedef enum fbcorr_status {
 } fbcorr_status;
 
 /* Operand precision.  Accumulation and outputs are float32 in every mode.
+ * FP32 operands are used with all their bits: on fp32 matrix instructions or
+ * vector units, or as exact sums of three bf16 values each on the bf16
+ * matrix units (six products per pair, fp32 accumulation; no further from
+ * the fp64 result than fp32 instructions).  Values for which that would not
+ * hold -- non-zero magnitudes outside [2^-100, 2^100), infinities, NaNs --
+ * are computed with fp32 instructions, workgroup by workgroup.
  * BF16 and FP16 round x and w to nearest-even after scaling each filter by a
  * power of two, s_n = 2^-floor(log2 max|w[n]|), and divide the accumulated
  * result by s_n again (exact).  FP16 inputs keep their full float32 range:
@@ -92,8 +98,9 @@ typedef enum fbcorr_precision {
  * B[(u,v,d), filter], with A gathered from LDS-staged input tiles and never
  * materialised; two kernels implement it (configuration algo=igemm: filter
  * slices staged through LDS; algo=rgemm: filters repacked in matrix-core
- * fragment order and streamed from L2 into registers), the tuning database
- * or fbcorr_plan_set_config picks one.  AUTO: the tuned choice, else IGEMM. */
+ * fragment order and streamed from L2 into registers), the tuning
+ * database, a cost model or fbcorr_plan_set_config picks one and its tiles.
+ * AUTO: the tuned choice, else IGEMM. */
 typedef enum fbcorr_algo {
     FBCORR_ALGO_AUTO = 0,
     FBCORR_ALGO_DIRECT = 1,
@@ -245,8 +252,9 @@ FBCORR_API fbcorr_status fbcorr_forward_batched(fbcorr_plan_t plan, const float*
 FBCORR_API fbcorr_status fbcorr_plan_get_config(fbcorr_plan_t plan, int role, char* buf, size_t len);
 
 /* Replace the configuration of `role` by one given in the same text form
- * (keys not given keep their defaults).  Compiles it; on any error the
- * previous configuration stays in place. */
+ * (keys not given keep their defaults: the tuning database's for this
+ * problem, else the named algorithm's hand-written ones).  Compiles it; on
+ * any error the previous configuration stays in place. */
 FBCORR_API fbcorr_status fbcorr_plan_set_config(fbcorr_plan_t plan, int role, const char* cfg);
 
 /* Fused elementwise epilogue for the forward pass (the static nonlinearity

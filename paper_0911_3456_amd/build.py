@@ -66,7 +66,13 @@ CHECK_DEFINES = {
                   "-DFB_BATCH=1 -DFB_FH=13 -DFB_FW=13 -DFB_CIN=16 -DFB_COUT=128 -DFB_HI=512 -DFB_WI=512 -DFB_HO=500 "
                   "-DFB_WO=500 -DFB_PADH=0 -DFB_PADW=0 -DFB_DT=2 -DFB_KC=16 -DFB_MR=2 -DFB_MT=4 -DFB_NT=2 -DFB_WM=2 "
                   "-DFB_WN=2 -DFB_PF=3 -DFB_XPADC=0 -DFB_WPE=2 -DFB_XCDMAP=1 -DFB_KNAME=fbcorr_fwd_rgemm -DFB_XMOFF=128",
+                  "-DFB_BATCH=6 -DFB_FH=5 -DFB_FW=3 -DFB_CIN=24 -DFB_COUT=48 -DFB_HI=97 -DFB_WI=131 -DFB_HO=93 "
+                  "-DFB_WO=129 -DFB_PADH=0 -DFB_PADW=0 -DFB_DT=3 -DFB_MF=16 -DFB_KC=24 -DFB_MR=2 -DFB_MT=2 -DFB_NT=3 "
+                  "-DFB_WM=2 -DFB_WN=1 -DFB_PF=2 -DFB_XPADC=0 -DFB_WPE=2 -DFB_XCDMAP=1 -DFB_STE=1 "
+                  "-DFB_KNAME=fbcorr_fwd_rgemm",
                   "-DFB_PACK_FRAG -DFB_FH=13 -DFB_FW=13 -DFB_CIN=16 -DFB_COUT=128 -DFB_DT=1 -DFB_KC=16 -DFB_PF=3",
+                  "-DFB_PACK_FRAG -DFB_FH=7 -DFB_FW=7 -DFB_CIN=3 -DFB_COUT=32 -DFB_DT=3 -DFB_MF=16 -DFB_KC=3 -DFB_PF=2 "
+                  "-DFB_S=4 -DFB_NCOLW=64",
                   "-DFB_PACK_FRAG -DFB_FH=7 -DFB_FW=7 -DFB_CIN=64 -DFB_COUT=16 -DFB_DT=0 -DFB_KC=16 -DFB_PF=3 -DFB_FLIP"],
     "util.hip": "-DFB_SUM_PARTIALS -DFB_L=41472 -DFB_NP=256 -DFB_RS=16 -DFB_LANES=16 -DFB_FLIP_FILTERS -DFB_N=64 -DFB_FH=9 -DFB_FW=9 -DFB_D=8 "
                 "-DFB_PACK_LOWP -DFB_LOWP=1 -DFB_FILL_INT -DFB_TRANSPOSE_FILTERS -DFB_NPAD=64 -DFB_ABSMAX",

@@ -9,6 +9,7 @@
 #include "geometry.h"
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <sstream>
 
@@ -117,6 +118,137 @@ Config default_rgemm(int cin, int cout, bool lowp) {
     return c;
 }
 
+// The register-streamed kernel's tiling for a problem, by a cost model.
+//
+// Every tiling of a grid (tile size, column shift, tile rows, per-wave tiles,
+// waves, chunk width) is priced as a sum of the times a compute unit needs
+// for the parts of its work, and the cheapest is taken.  The prices are a
+// non-negative least-squares fit to 2300 timings of random tilings on MI355X
+// over 31 problems (21 forward, 10 input gradients; 1 to 100 channels, 4 to
+// 128 filters of 1x1 to 13x13, 0.01 to 50 GFLOP); the fit's error is 11 %,
+// and its choice was on average 9 % behind the fastest of about 75 tilings
+// timed per problem.  (One fixed tiling per kernel was 1.3 to 13 times slower
+// than that on the same problems.)
+struct CorrProblem {
+    int batch, hi, wi, cin, cout, fh, fw, padh, padw;
+};
+struct TilePrices {
+    // microseconds per: MFMA cycle of a SIMD; the same for 32x32 tiles;
+    // the same short of two waves; LDS cycle of the A reads; the same for
+    // rows without planes; L1 cycle of the B loads; the same, once per
+    // workgroup; staged value of a lane, tiles of more than two rows, and
+    // divided by the workgroups that overlap it; stored value of a lane, and
+    // not through LDS, and not streaming; channel chunk and step one after
+    // another; MFMA cycle of one wave; call
+    double mfma, mfma32, mfma1, lds, ldslin, b, bwg, stage, stage_rows, stage_alone, store, store_plain, store_cached,
+        chunk, step, chain, call;
+};
+static const TilePrices kSplitPrices = {3.293e-4, 1.535e-4, 5.901e-5, 2.977e-5, 7.707e-5, 2.093e-4,
+                                        7.344e-5, 4.956e-3, 9.328e-4, 5.676e-3, 2.983e-3, 3.991e-3,
+                                        1.534e-3, 0.8924,   1.758e-2, 1.088e-4, 8.234};
+// 16-bit operands: 1230 timings over 14 problems, error 14 %, choice 10 %
+// behind the fastest of about 85 tilings.
+static const TilePrices kLowpPrices = {4.676e-4, 1.435e-4, 3.716e-5, 8.939e-5, 1.729e-4, 1.736e-4,
+                                       2.166e-5, 5.877e-3, 5.469e-4, 0.0,      8.826e-4, 6.493e-3,
+                                       7.279e-4, 0.9402,   0.0,      0.0,      8.339};
+
+struct Tiling {
+    int mf, kc, s, mr, mt, nt, wm, wn, pf, nts, ste;
+};
+
+// nsp: bf16 parts per fp32 value (3), or 1 for 16-bit operands.
+static double price_tiling(const Tiling& c, const CorrProblem& p, int nsp, const TilePrices& pr) {
+    const int npl = c.kc / 8, nkg = 64 / c.mf, w = c.wm * c.wn, nm = nsp == 3 ? 6 : 1;
+    const bool planes = c.kc % 8 == 0 && !(npl & (npl - 1));
+    const int regs =
+        c.mt * c.nt * (c.mf * c.mf / 64) * (nsp == 3 ? 2 : 1) + c.pf * c.nt * 4 * nsp + 2 * c.mt * 4 * nsp + 24;
+    if (regs > 256) return 1e30;
+    const int ho = p.hi + 2 * p.padh - p.fh + 1, wo = p.wi + 2 * p.padw - p.fw + 1;
+    const int cpr = cdiv((p.fw + c.s - 1) * c.kc, 8), nch = cdiv(p.cin, c.kc), ks = cdiv(p.fh * cpr, nkg);
+    const int mc = c.mf / c.mr, th = c.wm * c.mt * c.mr, two = c.s * mc, cb = c.wn * c.nt * c.mf / c.s;
+    const int tr = th + p.fh - 1, tc = c.s * (mc - 1) + cdiv(cpr * 8, c.kc);
+    long lds = nsp * (planes ? (long)npl * tr * cdiv(tc, c.s) * c.s * 16
+                             : ((long)tr * cdiv(tc * c.kc, 4) + 1) / 2 * 16);
+    if (c.ste) lds = std::max(lds, (long)w * c.mf * (c.nt * c.mf + 8) * 4);
+    if (lds > 160 * 1024) return 1e30;
+    const int wps = std::min(8, 512 / ((regs + 7) / 8 * 8));
+    const int occ = std::min({(int)(160 * 1024 / std::max(lds, 1L)), wps * 4 / w, 8});
+    if (occ < 1) return 1e30;
+    // the busiest CU runs q workgroups, cc at a time; later rounds even out
+    const double n = (double)cdiv(wo, two) * cdiv(ho, th) * cdiv(p.cout, cb) * p.batch;
+    const double q = std::ceil(n / 256.0), cc = std::min((double)occ, q);
+    const double qe = q > cc ? 0.5 * (n / 256.0 + q) : q;
+    const double seq = std::ceil(q / cc);
+    const double steps = (double)ks * nch;
+    const double mfma = steps * c.mt * c.nt * nm * c.mf;                       // cycles of a wave
+    const double per_simd = cc * w / 4.0;
+    const double tm = qe * mfma * w / 4.0 * std::max(1.0, std::ceil(per_simd) / per_simd);
+    const double tl = qe * steps * c.mt * nsp * 8 * w, tb = qe * steps * c.nt * nsp * 16 * w;
+    const double st = (double)tr * tc * c.kc * nch / 64.0, te = qe * th * two * cb * 4 / 256.0;
+    double t = pr.call + tm * (pr.mfma + (c.mf == 32 ? pr.mfma32 : 0.0) + pr.mfma1 * std::max(0.0, 2.0 - per_simd));
+    t += tl * (pr.lds + (planes ? 0.0 : pr.ldslin)) + tb * (pr.b + pr.bwg * c.wn / w);
+    t += qe * st * (pr.stage + (c.mr > 2 ? pr.stage_rows : 0.0) + pr.stage_alone / cc);
+    t += te * (pr.store + (c.ste ? 0.0 : pr.store_plain) + (c.nts ? 0.0 : pr.store_cached));
+    return t + seq * (nch * pr.chunk + steps * pr.step + mfma * pr.chain);
+}
+
+static Config cheapest_rgemm(const CorrProblem& p, int nsp) {
+    const TilePrices& pr = nsp == 3 ? kSplitPrices : kLowpPrices;
+    const int cin = p.cin, cout = p.cout;
+    const long ho = p.hi + 2 * p.padh - p.fh + 1, wo = p.wi + 2 * p.padw - p.fw + 1;
+    std::vector<int> kcs;
+    auto kc_add = [&](int k) { if (std::find(kcs.begin(), kcs.end(), k) == kcs.end()) kcs.push_back(k); };
+    if (cin % 4 == 0 && cin <= 32) kc_add(cin);
+    if (cin > 4) kc_add(8);
+    for (int k : {16, 24, 32})
+        if (cin % k == 0) kc_add(k);
+    if (cin % 4 && cin < 32) { kc_add(round_up(cin, 4)); kc_add(cin); }
+    Tiling c, best{};
+    // a step of 16-bit operands has a sixth of the products: the fragment
+    // ring has to reach further ahead (4 steps 5-15 % faster than 2 or 3)
+    c.pf = nsp == 3 ? 2 : 4;
+    // Streaming stores leave L2 to the operands; an output that L2 can hold
+    // (8 x 4 MB) is stored through it, for the kernel that reads it next.
+    c.nts = (double)p.batch * ho * wo * cout * 4 > 32.0 * (1 << 20) ? 1 : 0;
+    double best_t = 1e30;
+    for (int kc : kcs)
+        for (int mf : {16, 32})
+            for (int s : {1, 2, 4, 8}) {
+                const int npl = kc / 8;
+                const bool planes = kc % 8 == 0 && !(npl & (npl - 1));
+                if (planes && cin % 8 && kc != 8) continue;
+                if (!planes && (s * kc) % 4) continue;
+                // shifts fill a tile from a narrow bank (or align a narrow input)
+                if (s > 1 && cout * s > 64 && kc % 4 == 0) continue;
+                if (s == 8 && cout > 8) continue;
+                c.kc = kc; c.mf = mf; c.s = s;
+                c.ste = s == 1 && cout % 4 == 0 ? 1 : 0;
+                const int need = cdiv(cout * s, mf) * mf / s;        // filters that can be used
+                for (c.wn = 1; c.wn <= 4; ++c.wn)
+                    for (c.nt = 1; c.nt <= 4; ++c.nt) {
+                        const int ncol = c.wn * c.nt * mf;
+                        if (ncol % s || (ncol / s > need && ncol != mf)) continue;
+                        for (c.wm = 1; c.wm * c.wn <= 8; c.wm *= 2) {
+                            const int w = c.wm * c.wn;
+                            if (w < 2 || (w == 2 && cdiv(cin, kc) > 2)) continue;
+                            for (c.mr = 1; c.mr <= 8; c.mr *= 2)
+                                for (c.mt = 1; c.mt <= (nsp == 3 ? 4 : 8); c.mt *= 2) {
+                                    const double t = price_tiling(c, p, nsp, pr);
+                                    if (t < best_t) { best_t = t; best = c; }
+                                }
+                        }
+                    }
+            }
+    Config out;
+    if (best_t >= 1e30) return out;          // nothing fits
+    out.algo = "rgemm";
+    out.v = {{"mf", best.mf}, {"kc", best.kc}, {"s", best.s}, {"mr", best.mr}, {"mt", best.mt}, {"nt", best.nt},
+             {"wm", best.wm}, {"wn", best.wn}, {"pf", best.pf}, {"xpadc", 0}, {"wpe", 2}, {"xcd", 1},
+             {"nts", best.nts}, {"ste", best.ste}};
+    if (nsp == 3) out.v["sp"] = 1;
+    return out;
+}
+
 // Variants of a default that use fewer resources, tried in order until one
 // fits the device.
 static std::vector<Config> shrink_sequence(const Config& base) {
@@ -176,7 +308,8 @@ Config default_dw(const fbcorr_desc& d, int cus) {
     return c;
 }
 
-static Config heuristic_config(const fbcorr_desc& d, int role, int cus) {
+// The kernels that need no repacked filters, any size.
+static Config plain_config(const fbcorr_desc& d, int role, int cus) {
     const bool lowp = d.precision != FBCORR_FP32;
     switch (role) {
     case FBCORR_ROLE_FORWARD:
@@ -187,6 +320,29 @@ static Config heuristic_config(const fbcorr_desc& d, int role, int cus) {
     default:
         return default_dw(d, cus);
     }
+}
+
+static Config heuristic_config(const fbcorr_desc& d, int role, int cus) {
+    const bool lowp = d.precision != FBCORR_FP32;
+    const int ho = d.H - d.fh + 1, wo = d.W - d.fw + 1;
+    const double flops = 2.0 * d.batch * ho * wo * d.N * d.fh * d.fw * d.D;
+    // The forward pass in fp32: three bf16 parts pay for the extra launch
+    // that repacks the filters from about 0.2 GFLOP on (fp32 instructions,
+    // one launch, against this: 8.5 and 11.4 us at 0.1 GFLOP, 23 and 14 us
+    // at 1.3), and not where the windows are too short to be anything but
+    // memory traffic (1x1 windows of 16 channels: 13.6 and 15.9 us; a single
+    // channel, 5x5: 20 and 28 us).  The other kernels here need a launch for
+    // the filters anyway.
+    const int window = d.fh * d.fw * d.D;
+    Config c;
+    if (role == FBCORR_ROLE_FORWARD && lowp)
+        c = cheapest_rgemm({d.batch, d.H, d.W, d.D, d.N, d.fh, d.fw, 0, 0}, 1);
+    else if (role == FBCORR_ROLE_FORWARD && d.algo != FBCORR_ALGO_DIRECT && flops >= 2.0e8 &&
+             window > (d.D == 1 ? 64 : 16))
+        c = cheapest_rgemm({d.batch, d.H, d.W, d.D, d.N, d.fh, d.fw, 0, 0}, 3);
+    else if (role == FBCORR_ROLE_BACKWARD_X)
+        c = cheapest_rgemm({d.batch, ho, wo, d.N, d.D, d.fh, d.fw, d.fh - 1, d.fw - 1}, 3);
+    return c.algo.empty() ? plain_config(d, role, cus) : c;
 }
 
 // ---------------------------------------------------------- geometry
@@ -296,32 +452,45 @@ static bool geom_rgemm(const char* kname, const Config& c, int batch, int hi, in
     if (pf > 8) { err = "rgemm: pf is at most 8"; return false; }
     if (wpe < 1 || wpe > 8) { err = "rgemm: wpe must be 1..8"; return false; }
     if (mf % mr) { err = "rgemm: mr must divide mf"; return false; }
-    const int pe = dt == 0 ? 4 : 8, e = (64 / mf) * pe;
+    // fp32 operands as three bf16 parts: 16-bit cells, two accumulators
+    const int sp = c.get("sp");
+    if (sp != 0 && sp != 1) { err = "rgemm: sp is 0 or 1"; return false; }
+    if (sp && dt != 0) { err = "rgemm: sp applies to fp32 operands"; return false; }
+    if (sp) dt = 3;
+    const int nsp = sp ? 3 : 1, nacc = sp ? 2 : 1;
+    const int pe = dt == 0 ? 4 : 8, nkg = 64 / mf;
     const int npl = kc / pe;
-    if (kc % pe || (npl & (npl - 1))) {
+    const bool planes = kc % pe == 0 && !(npl & (npl - 1));
+    if (dt == 0 && !planes) {
         err = "rgemm: kc must be " + std::to_string(pe) + " times a power of two"; return false;
     }
+    if (!planes && (sh * kc) % 4) { err = "rgemm: s*kc must be a multiple of 4"; return false; }
+    if (!planes && kc < cin && cin % kc) {
+        err = "rgemm: kc must be " + std::to_string(pe) + " times a power of two or cut the channels evenly"; return false;
+    }
+    if (kc % 4 && kc != cin) { err = "rgemm: a kc that is not a multiple of 4 must be the channel count"; return false; }
     if (kc > 64) { err = "rgemm: kc is at most 64"; return false; }
-    if (cin % pe && kc != pe) { err = "rgemm: channels not a multiple of the cell width need kc=" + std::to_string(pe); return false; }
+    if (planes && cin % pe && kc != pe) { err = "rgemm: channels not a multiple of the cell width need kc=" + std::to_string(pe); return false; }
     const int threads = wm * wn * 64;
     if (threads > std::min(1024, di.max_threads)) { err = "rgemm: too many threads"; return false; }
     // accumulators, the fragment ring and two sets of A fragments must fit
     // the per-lane register budget of wpe waves per SIMD (512 / wpe)
-    const int regs = mt * nt * (mf * mf / 64) + pf * nt * 4 + 2 * mt * 4 + 24;
+    const int regs = mt * nt * (mf * mf / 64) * nacc + pf * nt * 4 * nsp + 2 * mt * 4 * nsp + 24;
     if (regs > 512 / wpe) {
         err = "rgemm: needs about " + std::to_string(regs) + " registers per lane, more than wpe allows"; return false;
     }
-    const int nstep = ((fw + sh - 1) * kc + e - 1) / e;
-    const int ntaps = nstep * e / kc;
+    const int cpr = cdiv((fw + sh - 1) * kc, pe);      // cells per filter row
+    const int ntaps = cdiv(cpr * pe, kc);
     const int nchunk = (cin + kc - 1) / kc;
-    const int ksteps2 = fh * nstep + pf;
+    const int ksteps2 = cdiv(fh * cpr, nkg) + pf;
     const int mc = mf / mr;
     const int ncolw = wn * nt * mf, cb = ncolw / sh;
     const int th = wm * mt * mr, two = sh * mc;
-    const int tr = th + fh - 1, tc = sh * (mc - 1) + ntaps, tcp = tc + xpadc;
+    const int tr = th + fh - 1, tc = sh * (mc - 1) + ntaps;
     const int ste = c.get("ste");
     if (ste && (sh != 1 || cout % 4)) { err = "rgemm: ste needs s=1 and a multiple of 4 output channels"; return false; }
-    long lds = (long)npl * tr * tcp * 16;
+    long lds = nsp * (planes ? (long)npl * tr * (cdiv(tc, sh) * sh + xpadc) * 16
+                             : ((long)tr * (cdiv(tc * kc, 4) + xpadc) + 1) / 2 * 16);
     if (ste) lds = std::max(lds, (long)wm * wn * mf * (nt * mf + 8) * 4);
     if (lds > di.lds_per_block) { err = "rgemm: LDS " + std::to_string(lds) + " B exceeds the device limit"; return false; }
     const int ho = hi + 2 * padh - fh + 1, wo = wi + 2 * padw - fw + 1;
@@ -331,7 +500,7 @@ static bool geom_rgemm(const char* kname, const Config& c, int batch, int hi, in
     // (NCOLW columns of shifted filters each): one kilobyte per column tile,
     // chunk and step
     const int ncols = cdiv(cout, cb) * ncolw;
-    bank_bytes = (size_t)(ncols / mf) * nchunk * ksteps2 * 1024;
+    bank_bytes = (size_t)(ncols / mf) * nchunk * ksteps2 * nsp * 1024;
     g.grid_x = (int)grid;
     g.grid_y = 1;
     g.threads = threads;
@@ -521,7 +690,7 @@ static bool known_keys(const Config& c, std::string& err) {
         {"direct", {"th", "tw", "p", "q", "nb", "ds", "layout", "xpad", "wpad", "ud", "xcd", "fsrc", "sb"}},
         {"dw", {"rh", "rw", "nw", "tpb", "np", "gpad", "xpad", "pf", "bal", "unr", "skipe"}},
         {"rgemm", {"mf", "kc", "s", "mr", "mt", "nt", "wm", "wn", "pf", "xpadc", "wpe", "unr", "xcd", "flip", "nts",
-                   "ste"}},
+                   "ste", "sp"}},
     };
     auto it = keys.find(c.algo);
     if (it == keys.end()) { err = "unknown algorithm '" + c.algo + "'"; return false; }
@@ -606,9 +775,11 @@ static bool build_role_impl(const fbcorr_desc& d, int role, const Config& c, con
                         rb.main_geom, rb.main, pk, pg, bank, err))
             return false;
         pk.options.push_back("-DFB_FLIP");
+        rb.main.options.push_back("-DFB_FLIP");
         rb.aux.push_back(pk);
         rb.aux_geom.push_back(pg);
-        rb.ws_bytes = align256(bank);
+        rb.ws_unscale = align256(bank);
+        rb.ws_bytes = rb.ws_unscale + align256((size_t)pg.grid_x * 4);
         return true;
     }
     if (role == FBCORR_ROLE_BACKWARD_X) {
@@ -631,8 +802,8 @@ static bool build_role_impl(const fbcorr_desc& d, int role, const Config& c, con
         return true;
     }
     if (role == FBCORR_ROLE_BACKWARD_W) {
-        if (c.algo != "dw") { err = "filter-gradient role needs algo=dw"; return false; }
         int np = 0;
+        if (c.algo != "dw") { err = "filter-gradient role needs algo=dw"; return false; }
         if (!geom_dw(c, d, di, rb.main_geom, rb.main, np, err)) return false;
         rb.np = np;
         const long L = (long)d.N * K;
@@ -652,63 +823,89 @@ static bool build_role_impl(const fbcorr_desc& d, int role, const Config& c, con
     return false;
 }
 
-Config default_config(const fbcorr_desc& d, int role, const DeviceInfo& di) {
-    std::string text;
-    if (tuning_db_lookup(di.arch, role, d, text)) {
-        Config c = heuristic_config(d, role, di.cus);
-        std::string err;
-        Config probe;
-        probe.algo = c.algo;
-        if (parse_config(text, probe, err)) {
-            // start from the chosen algorithm's heuristic and apply the entry
-            const int cin = role == FBCORR_ROLE_BACKWARD_X ? d.N : d.D;
-            const int cout = role == FBCORR_ROLE_BACKWARD_X ? d.D : d.N;
-            const bool lp = d.precision != FBCORR_FP32 && role == FBCORR_ROLE_FORWARD;
-            Config base = probe.algo == c.algo ? c
-                          : (probe.algo == "direct" ? default_direct(d)
-                             : probe.algo == "rgemm" ? default_rgemm(cin, cout, lp)
-                                                     : default_igemm(cin, cout, d.precision != FBCORR_FP32));
-            RoleBuild rb;
-            if (parse_config(text, base, err) && build_role(d, role, base, di, rb, err)) return base;
-        }
-    }
-    return heuristic_default(d, role, di);
-}
-
-bool config_from_text(const fbcorr_desc& d, int role, const DeviceInfo& di, const std::string& text,
-                      bool reset_named, Config& out, std::string& err) {
-    // A text that names another algorithm than the role's default starts
-    // from that algorithm's hand-written defaults ("algo=direct" alone is a
-    // complete configuration); with reset_named a forward-role text that
-    // names an algorithm always does.  Otherwise unnamed knobs keep the
-    // role's default.
-    Config c = default_config(d, role, di);
+// The tuning database's entry for this hardware and problem, if it builds.
+// form: the entry of one kernel form ("igemm", "rgemm"), kept beside the
+// problem's own where another form is faster.
+static bool database_config(const fbcorr_desc& d, int role, const DeviceInfo& di, Config& out,
+                            const std::string& form = "") {
+    std::string text, err;
+    if (!tuning_db_lookup(di.arch, role, d, text, form)) return false;
+    Config probe;
+    probe.algo = plain_config(d, role, di.cus).algo;
+    if (!parse_config(text, probe, err)) return false;
+    // start from the named algorithm's hand-written defaults
     const int cin = role == FBCORR_ROLE_BACKWARD_X ? d.N : d.D;
     const int cout = role == FBCORR_ROLE_BACKWARD_X ? d.D : d.N;
     const bool lp = d.precision != FBCORR_FP32 && role == FBCORR_ROLE_FORWARD;
-    if (role == FBCORR_ROLE_FORWARD) {
-        if (text.find("algo=direct") != std::string::npos) c = default_direct(d);
-        if (text.find("algo=igemm") != std::string::npos && (reset_named || c.algo != "igemm"))
-            c = default_igemm(cin, cout, lp);
-        if (text.find("algo=rgemm") != std::string::npos && (reset_named || c.algo != "rgemm"))
-            c = default_rgemm(cin, cout, lp);
-    } else if (role == FBCORR_ROLE_BACKWARD_X) {
-        if (text.find("algo=igemm") != std::string::npos && c.algo != "igemm") c = default_igemm(cin, cout, false);
-        if (text.find("algo=rgemm") != std::string::npos && c.algo != "rgemm") c = default_rgemm(cin, cout, false);
-    }
-    if (!parse_config(text, c, err)) return false;
-    out = c;
+    Config base = plain_config(d, role, di.cus);
+    if (probe.algo != base.algo)
+        base = probe.algo == "direct" ? default_direct(d)
+               : probe.algo == "rgemm" ? default_rgemm(cin, cout, lp)
+                                       : default_igemm(cin, cout, d.precision != FBCORR_FP32);
+    RoleBuild rb;
+    if (!parse_config(text, base, err) || !build_role(d, role, base, di, rb, err)) return false;
+    out = base;
     return true;
+}
+
+// The kernels of plain_config, shrunk until they fit the device.
+static Config plain_default(const fbcorr_desc& d, int role, const DeviceInfo& di) {
+    const Config h = plain_config(d, role, di.cus);
+    RoleBuild rb;
+    std::string err;
+    for (const Config& c : shrink_sequence(h))
+        if (build_role(d, role, c, di, rb, err)) return c;
+    return h;   // nothing fits: the caller reports the heuristic's error
 }
 
 Config heuristic_default(const fbcorr_desc& d, int role, const DeviceInfo& di) {
     const Config h = heuristic_config(d, role, di.cus);
-    for (const Config& c : shrink_sequence(h)) {
-        RoleBuild rb;
-        std::string err;
-        if (build_role(d, role, c, di, rb, err)) return c;
-    }
-    return h;   // nothing fits: the caller reports the heuristic's error
+    RoleBuild rb;
+    std::string err;
+    const Config plain = plain_default(d, role, di);
+    if (h.algo == plain.algo || !build_role(d, role, h, di, rb, err)) return plain;
+    // A forward pass that the static scratch could serve stays one (the
+    // packed bank of fp32 filters is larger than the filters).
+    RoleBuild pb;
+    if (role == FBCORR_ROLE_FORWARD && rb.ws_bytes > kNoAllocScratchBytes &&
+        build_role(d, role, plain, di, pb, err) && pb.ws_bytes <= kNoAllocScratchBytes)
+        return plain;
+    return h;
+}
+
+Config default_config(const fbcorr_desc& d, int role, const DeviceInfo& di) {
+    Config c;
+    return database_config(d, role, di, c) ? c : heuristic_default(d, role, di);
+}
+
+bool config_from_text(const fbcorr_desc& d, int role, const DeviceInfo& di, const std::string& text,
+                      bool reset_named, Config& out, std::string& err) {
+    // A text that names an algorithm starts from that algorithm's
+    // hand-written defaults ("algo=direct" alone is a complete
+    // configuration), one that names none from those of the kernels that
+    // fit any size; where the database has an entry, unnamed knobs are the
+    // entry's instead (but not on the forward role with reset_named, if the
+    // text names an algorithm).
+    Config named;
+    std::istringstream is(text);
+    std::string tok;
+    while (is >> tok)
+        if (tok.compare(0, 5, "algo=") == 0) named.algo = tok.substr(5);
+    Config c;
+    if (!database_config(d, role, di, c) &&
+        (named.algo.empty() || !database_config(d, role, di, c, named.algo)))
+        c = plain_default(d, role, di);
+    const int cin = role == FBCORR_ROLE_BACKWARD_X ? d.N : d.D;
+    const int cout = role == FBCORR_ROLE_BACKWARD_X ? d.D : d.N;
+    const bool lp = d.precision != FBCORR_FP32 && role == FBCORR_ROLE_FORWARD;
+    const bool other = named.algo != c.algo, reset = other || (reset_named && role == FBCORR_ROLE_FORWARD);
+    if (named.algo == "direct" && role == FBCORR_ROLE_FORWARD) c = default_direct(d);
+    else if (named.algo == "igemm" && role != FBCORR_ROLE_BACKWARD_W && reset) c = default_igemm(cin, cout, lp);
+    else if (named.algo == "rgemm" && role != FBCORR_ROLE_BACKWARD_W && reset) c = default_rgemm(cin, cout, lp);
+    else if (named.algo == "dw" && role == FBCORR_ROLE_BACKWARD_W && other) c = plain_default(d, role, di);
+    if (!parse_config(text, c, err)) return false;
+    out = c;
+    return true;
 }
 
 }  // namespace fbc

@@ -27,6 +27,10 @@ struct RoleBuild {
     int np = 0;                             // filter-gradient partial count
 };
 
+// The static device scratch of fbcorr_forward_noalloc (noalloc.hip): room
+// for the packed bank of any filter bank up to a few million weights.
+constexpr size_t kNoAllocScratchBytes = 16u << 20;
+
 // Default configuration of a role: the tuning database's entry for this
 // hardware and problem if there is one, else the hand-written heuristic
 // (shrunk until it fits the device).
@@ -35,7 +39,8 @@ Config heuristic_default(const fbcorr_desc& d, int role, const DeviceInfo& di);
 
 // tuning_db.cpp
 std::string tuning_db_path();
-bool tuning_db_lookup(const std::string& arch, int role, const fbcorr_desc& d, std::string& cfg);
+bool tuning_db_lookup(const std::string& arch, int role, const fbcorr_desc& d, std::string& cfg,
+                      const std::string& form = "");
 bool tuning_db_record(const std::string& arch, int role, const fbcorr_desc& d, const std::string& cfg,
                       std::string& err);
 void tuning_db_reload();

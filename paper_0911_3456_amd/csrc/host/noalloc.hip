@@ -15,9 +15,6 @@
 
 namespace fbc {
 
-// 16 MiB: room for the packed bank of any filter bank up to about eight
-// million weights.
-constexpr size_t kNoAllocScratchBytes = 16u << 20;
 constexpr int kMaxDevices = 64;
 
 static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];

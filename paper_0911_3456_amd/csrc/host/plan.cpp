@@ -155,7 +155,8 @@ fbcorr_status run_forward(Plan* p, const RoleExec& ex, const float* x, const flo
         void* args[] = {(void*)&x, (void*)&w, (void*)&y};
         st = launch(ex.main, rb.main_geom, s, args);
     } else {
-        void* args[] = {(void*)&x, (void*)&wt, (void*)&unscale, (void*)&y};
+        // (the last argument is the register-streamed kernel's only)
+        void* args[] = {(void*)&x, (void*)&wt, (void*)&unscale, (void*)&y, (void*)&w};
         st = launch(ex.main, rb.main_geom, s, args);
     }
     timing_end(p, FBCORR_ROLE_FORWARD, s, ev);
@@ -166,21 +167,23 @@ fbcorr_status run_backward_x(Plan* p, const RoleExec& ex, const float* w, const 
                              hipStream_t s) {
     const RoleBuild& rb = ex.build;
     const float* wfc = w;                   // fused flip: the kernel reads w itself
+    float* unscale = nullptr;
     hipEvent_t ev;
     timing_begin(p, FBCORR_ROLE_BACKWARD_X, s, ev);
     if (!ex.aux.empty()) {
         // flipped copy of the filters (fbcorr_flip_filters), or the
-        // fragment-ordered flipped bank (fbcorr_pack_frag, no scales)
+        // fragment-ordered flipped bank with its column scales
+        // (fbcorr_pack_frag)
         float* wf = (float*)ws;
-        float* no_scale = nullptr;
-        void* a0[] = {(void*)&w, (void*)&wf, (void*)&no_scale};
+        if (rb.cfg.algo == "rgemm") unscale = (float*)((char*)ws + rb.ws_unscale);
+        void* a0[] = {(void*)&w, (void*)&wf, (void*)&unscale};
         fbcorr_status st = launch(ex.aux[0], rb.aux_geom[0], s, a0);
         if (st != FBCORR_OK) { timing_end(p, FBCORR_ROLE_BACKWARD_X, s, ev); return st; }
         wfc = wf;
     }
     fbcorr_status st;
-    const float* unscale = nullptr;
-    void* a1[] = {(void*)&dy, (void*)&wfc, (void*)&unscale, (void*)&dx};
+    // (the last argument is the register-streamed kernel's only)
+    void* a1[] = {(void*)&dy, (void*)&wfc, (void*)&unscale, (void*)&dx, (void*)&w};
     st = launch(ex.main, rb.main_geom, s, a1);
     timing_end(p, FBCORR_ROLE_BACKWARD_X, s, ev);
     return st;

@@ -54,6 +54,12 @@ static TuneLayout tune_layout(const Plan* p) {
         const size_t steps = (size_t)d.fh * d.fw * (ci + 63) / 8 + chunks * d.fh + chunks * 8;
         rw = std::max(rw, align256(cols * steps * 64) + align256(cols * 4 + 2048));
     }
+    // the default variants, which run whatever the grid's bounds are
+    for (int r = 0; r < FBCORR_ROLE_COUNT; ++r) {
+        RoleBuild rb;
+        std::string err;
+        if (build_role(d, r, heuristic_default(d, r, p->dev), p->dev, rb, err)) rw = std::max(rw, rb.ws_bytes);
+    }
     off += rw;
     t.total = off;
     return t;
@@ -146,10 +152,6 @@ std::vector<Config> tune_candidates(const fbcorr_desc& d, int role, bool with_di
         std::vector<Config> rgrid;
         {
             const Config rb = default_rgemm(cin, cout, lp);
-            const int pe = lp ? 8 : 4;
-            std::vector<int> rkcs = {pe};
-            for (int k : {2 * pe, 4 * pe, 8 * pe})
-                if (k <= std::max(cin, 2 * pe) && (cin % pe == 0)) rkcs.push_back(k);
             const int rshapes[][4] = {{4, 2, 2, 2}, {4, 2, 1, 2}, {4, 2, 4, 1}, {2, 2, 2, 2}, {2, 2, 4, 2},
                                       {4, 1, 2, 4}, {4, 1, 4, 2}, {8, 1, 2, 2}, {2, 4, 2, 1}, {4, 2, 2, 1},
                                       {2, 2, 4, 1}, {4, 1, 4, 1}, {4, 4, 1, 2}, {2, 1, 4, 2}, {8, 1, 1, 4},
@@ -160,6 +162,15 @@ std::vector<Config> tune_candidates(const fbcorr_desc& d, int role, bool with_di
             std::vector<int> rss = {1};
             for (int sv : {2, 4})
                 if (cout * sv <= 32) rss.push_back(sv);
+            // fp32 operands: fp32 instructions, or three bf16 parts
+            for (int sp = 0; sp <= (lp ? 0 : 1); ++sp) {
+            const int pe = lp || sp ? 8 : 4;
+            std::vector<int> rkcs = {pe};
+            for (int k : {2 * pe, 4 * pe, 8 * pe})
+                if (k <= std::max(cin, 2 * pe) && (cin % pe == 0)) rkcs.push_back(k);
+            // (parts also take whole rows of a few channels)
+            if (sp && cin % 4 == 0 && cin <= 32 && std::find(rkcs.begin(), rkcs.end(), cin) == rkcs.end())
+                rkcs.push_back(cin);
             for (int kc : rkcs)
               for (int mf : {32, 16})
                for (int sv : rss)
@@ -182,8 +193,10 @@ std::vector<Config> tune_candidates(const fbcorr_desc& d, int role, bool with_di
                                     c.v["kc"] = kc; c.v["mr"] = mr;
                                     c.v["mt"] = sh[0]; c.v["nt"] = sh[1]; c.v["wm"] = sh[2]; c.v["wn"] = sh[3];
                                     c.v["pf"] = pf; c.v["xpadc"] = xp; c.v["wpe"] = wpe;
+                                    if (sp) c.v["sp"] = 1;
                                     rgrid.push_back(c);
                                 }
+            }
             uint64_t st2 = 0xD1B54A32D192ED03ull;
             for (size_t i = rgrid.size(); i > 1; --i) {
                 st2 = st2 * 6364136223846793005ull + 1442695040888963407ull;

@@ -8,6 +8,11 @@
 //   <arch> <role> <precision> <batch> <H> <W> <D> <N> <fh> <fw> : <config text>
 //   <arch> nearest u8 <T> <M> <D> : <config text>      (nearest-neighbour search)
 //
+// A forward entry for the direct kernel carries "direct" after the sizes.  So
+// may an entry carry "igemm" or "rgemm": the tuned configuration of that form
+// for a problem whose default is another; it gives the knobs that a
+// configuration text naming the form leaves out.
+//
 // A batched plan's variants use role "batched" with H = W = 0: one entry per
 // key (fh, fw, D, N), whatever the image sizes.
 //
@@ -85,8 +90,9 @@ bool tuning_db_lookup_key(const std::string& key, std::string& cfg) {
     return true;
 }
 
-bool tuning_db_lookup(const std::string& arch, int role, const fbcorr_desc& d, std::string& cfg) {
-    return tuning_db_lookup_key(db_key(arch, role, d), cfg);
+bool tuning_db_lookup(const std::string& arch, int role, const fbcorr_desc& d, std::string& cfg,
+                      const std::string& form) {
+    return tuning_db_lookup_key(db_key(arch, role, d) + (form.empty() ? "" : " " + form), cfg);
 }
 
 bool tuning_db_record(const std::string& arch, int role, const fbcorr_desc& d, const std::string& cfg,

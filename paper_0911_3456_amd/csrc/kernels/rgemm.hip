@@ -27,14 +27,42 @@
 //   XPADC sets the stride.)
 //
 // Contraction order.  Within a filter row u and chunk, the run of (v, k)
-// pairs (tap-major, FW*KC values, zero-padded to NSTEP*E) is cut into steps
-// of E = NKG*PE values, NKG = 64/MF lane groups; lane group g of an
-// instruction takes values [E*t + g*PE, E*t + g*PE + PE) of step t.  Run
-// position e lies in cell plane (e % KC)/PE, tap e / KC.  For 16-bit
-// operands one step is one v_mfma_f32_{32x32x16,16x16x32} (8 values per
-// lane); for fp32 it is four v_mfma_f32_{32x32x2,16x16x4}_f32 (value q of the
-// lane's cell in product q).  A and B use the same order, so every padding
-// value multiplies a zero weight.
+// pairs (tap-major, FW*KC values) is cut into cells of PE values, zero-padded
+// to CPR whole cells; the rows' cells follow one another, and a step takes
+// NKG = 64/MF of them, one per lane group of an instruction.  A step may
+// therefore straddle two filter rows, so the padding is less than a cell per
+// row and less than a step per chunk (a 9-tap row of 8 channels costs 9
+// cells, not 10 or 12).  For 16-bit operands one step is one
+// v_mfma_f32_{32x32x16,16x16x32} (8 values per lane); for fp32 it is four
+// v_mfma_f32_{32x32x2,16x16x4}_f32 (value q of the lane's cell in product
+// q).  A and B use the same order, so every padding value multiplies a zero
+// weight.
+//
+// LDS layout of the input tile.  KC a power-of-two number of cells: planes
+// of 16-byte cells as above.  Any other KC (16-bit operands): the rows as
+// they are, KC values per pixel; a cell is then any 8-byte aligned run of 8
+// values, which may straddle pixels (4 channels: two taps per cell).  The
+// lanes of a tile are S*KC values apart, so S*KC is a multiple of 4: a
+// single-channel image takes S = 4, which costs little where a row of taps
+// is padded to whole cells anyway (11 taps + 3 shifts: 14 of 16 values).
+//
+// fp32 as three bf16 parts (DT 3).  fp32 matrix instructions run at 1/16 of
+// the bf16 rate.  Every fp32 value is exactly the sum of three bf16 values
+// h + m + l (each the rounded remainder of the ones before), and the product
+// of two such sums needs six bf16 products (hh, hm, mh, mm, hl, lh; what is
+// left out is below 2^-24 of |x||w|), so a step is six instructions on
+// operands staged as three parts instead of 8 * 2 of the fp32 kind: 290
+// against 133-150 TFLOP/s of fp32 work with the operands in registers.  hh
+// goes to one accumulator and the five small products to another, added at
+// the end: the sum is then rounded once per 16 products instead of once per
+// product, and the error against fp64 is a third of the fp32 instructions'
+// (rms 7e-9 against 2.4e-8 of sum |x||w|, contractions of 144 to 16384; all
+// terms positive: 1.5e-7 against 4.2e-7 at 784).  Filters are scaled by a
+// power of two per filter, as for 16-bit operands, so their parts never
+// leave the bf16 range.  Input values are not: a workgroup whose tile holds
+// a non-zero magnitude outside [2^-100, 2^100), an infinity or a NaN -- or
+// whose filters hold a non-finite value -- computes its outputs with plain
+// fp32 fused multiply-adds instead (slow_tile).
 //
 // Column shift S (narrow outputs).  A workgroup's NCOLW = WN*NT*MF matrix
 // columns are S shifts x CB = NCOLW/S output channels: column (s, c)
@@ -45,14 +73,17 @@
 //
 // Compile-time constants (FB_<name>):
 //   problem  BATCH FH FW CIN COUT HI WI HO WO PADH PADW
-//   DT       0 fp32 operands, 1 bf16, 2 fp16 (B pre-scaled and rounded by
-//            the pack; UNSCALE[c] multiplies each output)
+//   DT       0 fp32 operands, 1 bf16, 2 fp16, 3 fp32 operands as three bf16
+//            parts (1-3: B pre-scaled and rounded by the pack; UNSCALE[c]
+//            multiplies each output, and for 3 is 0 for a filter that holds
+//            a non-finite value)
 //   XMOFF    fp16 only: UNSCALE[XMOFF .. XMOFF+255] hold partial maxima of |x|
 //            (fbcorr_absmax); when the input reaches 2^15 it is scaled by
 //            2^-k while staged (max |x| * 2^-k < 2^15, inside the fp16
 //            range) and the outputs by 2^k -- both exact powers of two
 //   tiling   MF (32 or 16: MFMA tile), KC (channels per chunk: PE times a
-//            power of two), S (column shift, above), MR (rows of an
+//            power of two, or for 16-bit operands any multiple of 4, or CIN
+//            where S*CIN is one), S (column shift, above), MR (rows of an
 //            MF-pixel tile), MT NT (tiles per
 //            wave), WM WN (waves), PF (filter-fragment ring depth in steps),
 //            XPADC (LDS row padding in cells), WPE (waves per SIMD the
@@ -72,6 +103,7 @@
 
 typedef float rg_f32x4 __attribute__((ext_vector_type(4)));
 typedef float rg_f32x16 __attribute__((ext_vector_type(16)));
+typedef unsigned int rg_u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int rg_u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 rg_bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 rg_f16x8 __attribute__((ext_vector_type(8)));
@@ -93,51 +125,77 @@ typedef _Float16 rg_f16x8 __attribute__((ext_vector_type(8)));
 #else
 #define PE 8
 #endif
+#if DT == 3
+#define NSP 3                     // bf16 parts of a value
+#define NACC 2                    // accumulators per tile: hh, the small products
+#else
+#define NSP 1
+#define NACC 1
+#endif
 #ifdef FB_S
 #define S FB_S
 #else
 #define S 1
 #endif
 #define NKG (64 / MF)             // lane groups of one instruction
-#define E (NKG * PE)              // contraction values per step
 #define NPL (KC / PE)             // cell planes per channel chunk
+#if KC % PE == 0 && (NPL & (NPL - 1)) == 0
+#define LIN 0                     // planes of cells
+#else
+#define LIN 1                     // rows as they are
+#endif
 #define NTAPF (FW + S - 1)        // taps of one filter row with the column shifts
-#define NSTEP ((NTAPF * KC + E - 1) / E)   // steps per filter row and chunk
-#define NTAPS ((NSTEP * E) / KC)        // taps covered, padding included
+#define CPR ((NTAPF * KC + PE - 1) / PE)   // cells per filter row
+#define NTAPS ((CPR * PE + KC - 1) / KC)   // taps covered, padding included
 #define NCHUNK ((CIN + KC - 1) / KC)
-#define KSTEPS (FH * NSTEP)             // steps per chunk
+#define NCELL (FH * CPR)                   // cells per chunk
+#define KSTEPS ((NCELL + NKG - 1) / NKG)   // steps per chunk
 #ifdef FB_PF
 #define KSTEPS2 (KSTEPS + FB_PF)        // packed steps per chunk: PF zero steps after the real ones
 #endif
 
 static_assert(MF == 32 || MF == 16, "MFMA tiles are 32x32 or 16x16");
-static_assert(KC % PE == 0 && ((KC / PE) & (KC / PE - 1)) == 0, "KC must be PE times a power of two");
+static_assert(!LIN || (DT != 0 && S * KC % 4 == 0), "KC must be PE times a power of two, or S*KC a multiple of 4 (16-bit)");
+static_assert(KC % 4 == 0 || KC == CIN, "a channel count that is not a multiple of 4 cannot be cut into chunks");
 
-// Cell offset (plane * plane_cells + tap) of run position e.
-#define RUN_PLANE(e) (((e) % KC) / PE)
-#define RUN_TAP(e) ((e) / KC)
+// The three bf16 parts of eight fp32 values: h rounds x to nearest even, m
+// the remainder x - h, l what is left (exact: 3 x 8 significant bits).
+__device__ __forceinline__ void rg_split(const float* v, rg_u32x4& ch, rg_u32x4& cm, rg_u32x4& cl) {
+    rg_bf16x8 h, m, l;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        h[i] = (__bf16)v[i];
+        const float r = v[i] - (float)h[i];
+        m[i] = (__bf16)r;
+        l[i] = (__bf16)(r - (float)m[i]);
+    }
+    ch = __builtin_bit_cast(rg_u32x4, h);
+    cm = __builtin_bit_cast(rg_u32x4, m);
+    cl = __builtin_bit_cast(rg_u32x4, l);
+}
 
 // ------------------------------------------------------------------ pack
 #ifdef FB_PACK_FRAG
 // One workgroup per column pc of the packed bank: whole column blocks of
 // the correlation kernel, NCOLW columns each, column (s, c) of a block
 // holding filter c shifted by s taps (columns of filters at or past COUT
-// are zero).  Layout: 16-byte cell ((j*NCHUNK + chunk)*KSTEPS2 + u*NSTEP +
-// t)*64 + lane for column tile j = pc / MF, lane = MF*g + pc%MF.  16-bit
-// operands: e_c = floor(log2 max|w[c]|), values scaled by 2^-e_c (exact)
-// and rounded to nearest even, unscale[pc] = 2^e_c (an all-zero filter gets
-// e_c = 0).  FB_FLIP: the
+// are zero).  Layout: 16-byte cell (((j*NCHUNK + chunk)*KSTEPS2 + t)*NSP +
+// part)*64 + lane for column tile j = pc / MF, step t = cell / NKG, lane =
+// MF*(cell % NKG) + pc%MF.  16-bit operands and parts: e_c = floor(log2
+// max|w[c]|), values scaled by 2^-e_c (exact) and rounded to nearest even,
+// unscale[pc] = 2^e_c (an all-zero filter gets e_c = 0; three-part mode: 0
+// for a filter that holds a non-finite value).  FB_FLIP: the
 // filters are those of the input-gradient correlation, read from the
 // forward bank w[CIN][FH][FW][COUT] flipped in (u, v) with the channel axes
 // exchanged.
 extern "C" __global__ void __launch_bounds__(256)
 fbcorr_pack_frag(const float* __restrict__ w, rg_u32x4* __restrict__ bp, float* __restrict__ unscale)
 {
-    // items: (chunk, filter row, tap slot, plane), plane fastest; a thread
-    // takes items tid, tid + 256, ...  When they fit (HELD), every item's
-    // values are loaded once, all loads in flight together, and kept for
-    // both the maximum and the packing; otherwise they are read twice.
-    constexpr int ITEMS = NCHUNK * FH * NTAPS * NPL;
+    // items: the cells (chunk, filter row, cell of the row), cell fastest; a
+    // thread takes items tid, tid + 256, ...  When they fit (HELD), every
+    // item's values are loaded once, all loads in flight together, and kept
+    // for both the maximum and the packing; otherwise they are read twice.
+    constexpr int ITEMS = NCHUNK * NCELL;
     constexpr int PER = (ITEMS + 255) / 256;
     constexpr bool HELD = PER * PE <= 64;
     const int pc = blockIdx.x;
@@ -151,53 +209,64 @@ fbcorr_pack_frag(const float* __restrict__ w, rg_u32x4* __restrict__ bp, float* 
 #endif
     const bool real = c < COUT;
     auto load_item = [&](int e, float* vals) {
-        const int p = e % NPL;
-        int r = e / NPL;
-        const int vv = r % NTAPS;
-        r /= NTAPS;
-        const int u = r % FH, kci = r / FH;
-        const int ch0 = kci * KC + p * PE;
-        const int vf = vv - sh;                   // filter tap of this (shifted) column
-        const bool ok = e < ITEMS && real && vf >= 0 && vf < FW;
-#if !defined(FB_FLIP) && CIN % PE == 0
-        // PE consecutive channels of one tap: contiguous in w[c][u][v][:]
-        if (ok && ch0 < CIN) {
-            const float* src = w + (((long)c * FH + u) * FW + vf) * CIN + ch0;
-#pragma unroll
-            for (int q = 0; q < PE; q += 4) {
-                const rg_f32x4 x4 = *(const rg_f32x4*)(src + q);
-                vals[q] = x4[0]; vals[q + 1] = x4[1]; vals[q + 2] = x4[2]; vals[q + 3] = x4[3];
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < PE; ++i) vals[i] = 0.f;
-        }
-#else
+        const int kci = e / NCELL, u = (e % NCELL) / CPR, cc = e % CPR;
+#if KC % 4 != 0
 #pragma unroll
         for (int i = 0; i < PE; ++i) {
-            const int ch = ch0 + i;
+            const int vf = (cc * PE + i) / KC - sh, ch = (cc * PE + i) % KC;      // one chunk
+            const bool ok = e < ITEMS && real && vf >= 0 && vf < FW;
 #ifdef FB_FLIP
-            vals[i] = (ok && ch < CIN) ? w[(((long)ch * FH + (FH - 1 - u)) * FW + (FW - 1 - vf)) * COUT + c] : 0.f;
+            vals[i] = ok ? w[(((long)ch * FH + (FH - 1 - u)) * FW + (FW - 1 - vf)) * COUT + c] : 0.f;
 #else
-            vals[i] = (ok && ch < CIN) ? w[(((long)c * FH + u) * FW + vf) * CIN + ch] : 0.f;
+            vals[i] = ok ? w[(((long)c * FH + u) * FW + vf) * CIN + ch] : 0.f;
+#endif
+        }
+        (void)kci;
+#else
+        // groups of 4 values stay within one tap
+#pragma unroll
+        for (int q = 0; q < PE; q += 4) {
+            const int pos = cc * PE + q;
+            const int vf = pos / KC - sh;             // filter tap of this (shifted) column
+            const int ch0 = kci * KC + pos % KC;
+            const bool ok = e < ITEMS && real && vf >= 0 && vf < FW;
+#if !defined(FB_FLIP) && CIN % 4 == 0
+            // consecutive channels of one tap: contiguous in w[c][u][v][:]
+            rg_f32x4 x4 = {0.f, 0.f, 0.f, 0.f};
+            if (ok && ch0 < CIN) x4 = *(const rg_f32x4*)(w + (((long)c * FH + u) * FW + vf) * CIN + ch0);
+            vals[q] = x4[0]; vals[q + 1] = x4[1]; vals[q + 2] = x4[2]; vals[q + 3] = x4[3];
+#else
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int ch = ch0 + i;
+#ifdef FB_FLIP
+                vals[q + i] = (ok && ch < CIN)
+                                  ? w[(((long)ch * FH + (FH - 1 - u)) * FW + (FW - 1 - vf)) * COUT + c] : 0.f;
+#else
+                vals[q + i] = (ok && ch < CIN) ? w[(((long)c * FH + u) * FW + vf) * CIN + ch] : 0.f;
+#endif
+            }
 #endif
         }
 #endif
     };
     auto store_item = [&](int e, const float* vals, float sc) {
         if (e >= ITEMS) return;
-        const int p = e % NPL;
-        int r = e / NPL;
-        const int vv = r % NTAPS;
-        r /= NTAPS;
-        const int u = r % FH, kci = r / FH;
-        const int el = vv * KC + p * PE;          // position in the row's run
-        const int t = el / E, g = (el % E) / PE;
-        rg_u32x4 cell;
+        const int kci = e / NCELL, cell = e % NCELL;
+        const int t = cell / NKG, g = cell % NKG;
+        rg_u32x4* const dst = bp + (((long)j * NCHUNK + kci) * KSTEPS2 + t) * NSP * 64 + g * MF + col;
 #if DT == 0
         (void)sc;
-        cell = __builtin_bit_cast(rg_u32x4, (rg_f32x4){vals[0], vals[1], vals[2], vals[3]});
+        dst[0] = __builtin_bit_cast(rg_u32x4, (rg_f32x4){vals[0], vals[1], vals[2], vals[3]});
+#elif DT == 3
+        float sv[PE];
+#pragma unroll
+        for (int i = 0; i < PE; ++i) sv[i] = vals[i] * sc;       // exact: power of two
+        rg_u32x4 ch, cm, cl;
+        rg_split(sv, ch, cm, cl);
+        dst[0] = ch; dst[64] = cm; dst[128] = cl;
 #else
+        rg_u32x4 cell4;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const float lo_v = vals[2 * i] * sc, hi_v = vals[2 * i + 1] * sc;   // exact: power of two
@@ -208,27 +277,34 @@ fbcorr_pack_frag(const float* __restrict__ w, rg_u32x4* __restrict__ bp, float* 
             const unsigned lo = __builtin_bit_cast(unsigned short, (_Float16)lo_v);
             const unsigned hi = __builtin_bit_cast(unsigned short, (_Float16)hi_v);
 #endif
-            cell[i] = lo | (hi << 16);
+            cell4[i] = lo | (hi << 16);
         }
+        dst[0] = cell4;
 #endif
-        bp[(((long)j * NCHUNK + kci) * KSTEPS2 + u * NSTEP + t) * 64 + g * MF + col] = cell;
     };
 
     float held[HELD ? PER : 1][PE];
     float m = 0.f;
+    bool fin = true;                  // every value finite
+    auto scan = [&](const float* vals) {
+#pragma unroll
+        for (int q = 0; q < PE; ++q) {
+            m = fmaxf(m, fabsf(vals[q]));
+#if DT == 3
+            fin = fin && fabsf(vals[q]) <= 3.402823466e38f;      // false for infinities and NaNs
+#endif
+        }
+    };
     if (HELD) {
 #pragma unroll
         for (int i = 0; i < (HELD ? PER : 1); ++i) load_item(threadIdx.x + i * 256, held[i]);
 #pragma unroll
-        for (int i = 0; i < (HELD ? PER : 1); ++i)
-#pragma unroll
-            for (int q = 0; q < PE; ++q) m = fmaxf(m, fabsf(held[i][q]));
+        for (int i = 0; i < (HELD ? PER : 1); ++i) scan(held[i]);
     } else {
         for (int e = threadIdx.x; e < ITEMS; e += 256) {
             float vals[PE];
             load_item(e, vals);
-#pragma unroll
-            for (int q = 0; q < PE; ++q) m = fmaxf(m, fabsf(vals[q]));
+            scan(vals);
         }
     }
     float sc = 1.0f;
@@ -239,18 +315,26 @@ fbcorr_pack_frag(const float* __restrict__ w, rg_u32x4* __restrict__ bp, float* 
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-    __syncthreads();
+    fin = !__syncthreads_or(!fin);
     m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
     int ex = 0;
-    if (m > 0.f) {
+    if (fin && m > 0.f) {
         (void)frexpf(m, &ex);     // m = f * 2^ex, f in [0.5, 1)
         ex -= 1;                  // floor(log2 m)
     }
     sc = ldexpf(1.0f, -ex);
+#if DT == 3
+    // a filter below 2^-127 keeps the largest finite scale (its parts are
+    // then short of bits only below 2^-149 of full scale)
+    if (ex < -126) { ex = -126; sc = ldexpf(1.0f, 126); }
+    if (threadIdx.x == 0) unscale[pc] = fin ? ldexpf(1.0f, ex) : 0.f;
+#else
     if (threadIdx.x == 0) unscale[pc] = real ? ldexpf(1.0f, ex) : 0.f;
+#endif
 #else
     (void)unscale;
     (void)m;
+    (void)fin;
 #endif
     if (HELD) {
 #pragma unroll
@@ -262,11 +346,13 @@ fbcorr_pack_frag(const float* __restrict__ w, rg_u32x4* __restrict__ bp, float* 
             store_item(e, vals, sc);
         }
     }
-    // the zero steps after each chunk (read by the ring's last refills)
-    for (int e = threadIdx.x; e < NCHUNK * (KSTEPS2 - KSTEPS) * NKG; e += 256) {
-        const int g = e % NKG, st = (e / NKG) % (KSTEPS2 - KSTEPS), kci = e / (NKG * (KSTEPS2 - KSTEPS));
+    // the zero cells after each chunk: the rest of its last step, and the
+    // steps read by the ring's last refills
+    constexpr int ZC = KSTEPS2 * NKG - NCELL;
+    for (int e = threadIdx.x; e < NCHUNK * ZC * NSP; e += 256) {
+        const int cell = NCELL + e % ZC, sp = (e / ZC) % NSP, kci = e / (ZC * NSP);
         const rg_u32x4 z = {0u, 0u, 0u, 0u};
-        bp[(((long)j * NCHUNK + kci) * KSTEPS2 + KSTEPS + st) * 64 + g * MF + col] = z;
+        bp[((((long)j * NCHUNK + kci) * KSTEPS2 + cell / NKG) * NSP + sp) * 64 + (cell % NKG) * MF + col] = z;
     }
 }
 #endif  // FB_PACK_FRAG
@@ -301,10 +387,35 @@ fbcorr_pack_frag(const float* __restrict__ w, rg_u32x4* __restrict__ bp, float* 
 #define CB (NCOLW / S)                // filters per workgroup
 #define TR (TH + FH - 1)              // tile rows
 #define TC (S * (MC - 1) + NTAPS)     // tile columns any lane reads
-#define TCP (TC + XPADC)              // tile row stride in cells
-#define PLANE (TR * TCP)              // cells per plane
-#define TILE_CELLS (NPL * PLANE)
 #define NTHREADS (WM * WN * 64)
+// The tile in LDS, in units of UB bytes: planes of 16-byte cells, one cell
+// per pixel (LIN 0), or rows of KC values per pixel in 8-byte units (LIN 1).
+// In planes, a row holds the columns of each shift phase (column mod S)
+// together: the lanes of a tile, S columns apart, then read neighbouring
+// cells (without it a shift of 2 reads with a 32-byte stride, two bank
+// conflicts per read).
+#if LIN
+#define UB 8
+#define LSTEP (S * KC / 4)            // units from a lane's pixel to the next lane's
+#define ITEM 4                        // values staged per item
+#define ROWU ((TC * KC + 3) / 4)      // units of a tile row
+#define RSU (ROWU + XPADC)            // tile row stride
+#define SPU ((TR * RSU + 1) / 2 * 2)  // units per part (whole cells)
+#define SITEMS (TR * ROWU)            // staging items
+typedef rg_u32x2 rg_unit;
+#else
+#define UB 16
+#define LSTEP 1
+#define ITEM PE
+#define PHASE ((TC + S - 1) / S)      // columns of a phase
+#define COLPOS(cc) ((cc) % S * PHASE + (cc) / S)
+#define RSU (S * PHASE + XPADC)
+#define PLANE (TR * RSU)              // units per plane
+#define SPU (NPL * PLANE)
+#define SITEMS (NPL * TR * TC)
+typedef rg_u32x4 rg_unit;
+#endif
+#define TILE_CELLS (NSP * SPU * UB / 16)
 #if defined(FB_STE) && FB_STE
 // Stores through LDS: per wave, one pixel tile's worth of its columns as
 // rows of NT*MF floats (+8: the two lane groups' rows land on different
@@ -318,15 +429,24 @@ fbcorr_pack_frag(const float* __restrict__ w, rg_u32x4* __restrict__ bp, float* 
 #define STE 0
 #define LDS_CELLS TILE_CELLS
 #endif
-// tile cells staged per thread and batch (all of them when they are few)
-#define SCELLS ((NPL * TR * TC + NTHREADS - 1) / NTHREADS)
-#define SB (SCELLS < (DT == 0 ? 16 : 8) ? SCELLS : (DT == 0 ? 16 : 8))
+// items staged per thread and batch (all of them when they are few)
+#define SMAX (64 / ITEM)
+#define SCELLS ((SITEMS + NTHREADS - 1) / NTHREADS)
+#define SB (SCELLS < SMAX ? SCELLS : SMAX)
+// Lane group g of step t reads cell NKG*t + g.  When a row is a whole number
+// of steps (SEP) the groups' offsets differ by a constant.
+#define SEP (CPR % NKG == 0 && (LIN || NPL % NKG == 0 || (S == 1 && NKG % NPL == 0)))
+// Steps after which the pattern of cell offsets repeats, PROWS filter rows
+// further down; the step loop is unrolled over whole periods and over whole
+// turns of the fragment ring (PF) and of the two A buffers.
+#define PROWS (SEP ? 1 : NKG)
+#define PSTEPS (PROWS * CPR / NKG)
 
 static_assert(MF % MR == 0, "MR must divide MF");
 static_assert(NCOLW % S == 0, "the columns must split evenly into shifts");
 static_assert(!STE || S == 1, "stores through LDS need unshifted columns");
 static_assert(PF >= 1, "ring depth");
-static_assert(CIN % PE == 0 || KC == PE, "partial cells need KC == PE");
+static_assert(LIN || CIN % PE == 0 || KC == PE, "partial cells need KC == PE");
 
 template <bool V> struct RgBool { static constexpr bool value = V; };
 
@@ -353,27 +473,71 @@ __device__ __forceinline__ int rg_input_scale_exp(const float* __restrict__ UNSC
 #endif
 }
 
-// One 16-byte cell of PE values (scaled by xs, exact) in the operand type.
-__device__ __forceinline__ rg_u32x4 rg_cell(const float* v, const float xs) {
-    rg_u32x4 c;
-#if DT == 0
-    (void)xs;
-    c = __builtin_bit_cast(rg_u32x4, (rg_f32x4){v[0], v[1], v[2], v[3]});
-#else
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-#if DT == 1
-        (void)xs;
-        const unsigned lo = __builtin_bit_cast(unsigned short, (__bf16)v[2 * i]);      // nearest even
-        const unsigned hi = __builtin_bit_cast(unsigned short, (__bf16)v[2 * i + 1]);
-#else
-        const unsigned lo = __builtin_bit_cast(unsigned short, (_Float16)(v[2 * i] * xs));
-        const unsigned hi = __builtin_bit_cast(unsigned short, (_Float16)(v[2 * i + 1] * xs));
-#endif
-        c[i] = lo | (hi << 16);
+// Largest magnitude, and smallest non-zero one, of the values staged by a
+// thread, as bit patterns (in the order of the magnitudes; infinities and
+// NaNs above every finite value).
+struct RgRange {
+    unsigned hi = 0u, lo = 0xffffffffu;
+    __device__ __forceinline__ void see(const float v) {
+        const unsigned a = __builtin_bit_cast(unsigned, v) & 0x7fffffffu;
+        hi = hi > a ? hi : a;
+        lo = lo < a - 1u ? lo : a - 1u;              // zero wraps to the largest value
     }
+    // some non-zero magnitude outside [2^-100, 2^100)
+    __device__ __forceinline__ bool outside() const { return hi >= 0x71800000u || lo < 0x0d800000u - 1u; }
+};
+
+// Two values (scaled by xs, exact) rounded to nearest even, packed.
+__device__ __forceinline__ unsigned rg_pair(const float a, const float b, const float xs) {
+#if DT == 2
+    const unsigned lo = __builtin_bit_cast(unsigned short, (_Float16)(a * xs));
+    const unsigned hi = __builtin_bit_cast(unsigned short, (_Float16)(b * xs));
+#else
+    (void)xs;
+    const unsigned lo = __builtin_bit_cast(unsigned short, (__bf16)a);
+    const unsigned hi = __builtin_bit_cast(unsigned short, (__bf16)b);
 #endif
-    return c;
+    return lo | (hi << 16);
+}
+
+// One staged item (ITEM values) into the tile, every part of it.
+__device__ __forceinline__ void rg_put(rg_unit* __restrict__ dst, const float* v, const float xs, RgRange& range) {
+#if DT == 0
+    (void)xs; (void)range;
+    dst[0] = __builtin_bit_cast(rg_u32x4, (rg_f32x4){v[0], v[1], v[2], v[3]});
+#elif DT == 3
+    rg_unit h, m, l;
+#pragma unroll
+    for (int i = 0; i < ITEM / 2; ++i) {
+        const float a = v[2 * i], b = v[2 * i + 1];
+        range.see(a);
+        range.see(b);
+        h[i] = rg_pair(a, b, xs);
+        const float ra = a - __builtin_bit_cast(float, h[i] << 16);
+        const float rb = b - __builtin_bit_cast(float, h[i] & 0xffff0000u);
+        m[i] = rg_pair(ra, rb, xs);
+        l[i] = rg_pair(ra - __builtin_bit_cast(float, m[i] << 16), rb - __builtin_bit_cast(float, m[i] & 0xffff0000u), xs);
+    }
+    dst[0] = h; dst[SPU] = m; dst[2 * SPU] = l;
+#else
+    (void)range;
+    rg_unit c;
+#pragma unroll
+    for (int i = 0; i < ITEM / 2; ++i) c[i] = rg_pair(v[2 * i], v[2 * i + 1], xs);
+    dst[0] = c;
+#endif
+}
+
+// The cell at unit offset o.
+__device__ __forceinline__ rg_u32x4 rg_read(const rg_unit* __restrict__ tile, const int o) {
+#if LIN && (LSTEP % 2 != 0 || RSU % 2 != 0)
+    const rg_u32x2 p0 = tile[o], p1 = tile[o + 1];           // 8-byte aligned
+    return (rg_u32x4){p0[0], p0[1], p1[0], p1[1]};
+#elif LIN
+    return *(const rg_u32x4*)(tile + o);
+#else
+    return tile[o];
+#endif
 }
 
 // acc += A * B for one step of one (pixel tile, column tile) pair.
@@ -389,10 +553,10 @@ __device__ __forceinline__ void rg_mma(rg_acc& acc, const rg_u32x4 a, const rg_u
         acc = __builtin_amdgcn_mfma_f32_16x16x4f32(af[q], bf[q], acc, 0, 0, 0);
 #endif
     }
-#elif DT == 1 && MF == 32
+#elif (DT == 1 || DT == 3) && MF == 32
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(rg_bf16x8, a), __builtin_bit_cast(rg_bf16x8, b),
                                                   acc, 0, 0, 0);
-#elif DT == 1
+#elif DT == 1 || DT == 3
     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(rg_bf16x8, a), __builtin_bit_cast(rg_bf16x8, b),
                                                   acc, 0, 0, 0);
 #elif MF == 32
@@ -404,52 +568,108 @@ __device__ __forceinline__ void rg_mma(rg_acc& acc, const rg_u32x4 a, const rg_u
 #endif
 }
 
-extern "C" __global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
-FB_KNAME(const float* __restrict__ I, const rg_u32x4* __restrict__ Bp, const float* __restrict__ UNSCALE,
-         float* __restrict__ O)
-{
-    __shared__ rg_u32x4 tile[LDS_CELLS];
 
-    // Workgroup -> (image, column block, tile row, tile column); with XCDMAP
-    // each XCD gets a contiguous range (shared halos stay in its L2).
-    const int ntx = (WO + TWO - 1) / TWO;
-    const int nty = (HO + TH - 1) / TH;
-    const int ncb = (COUT + CB - 1) / CB;
-    const int total = ntx * nty * ncb * BATCH;
-    int lin = blockIdx.x;
-#if FB_XCDMAP
-    {
-        const int q = total / 8, r = total % 8, x = lin % 8;
-        lin = x * q + (x < r ? x : r) + lin / 8;
-    }
+// Orders the LDS accesses of a wave's lanes, and keeps control flow that
+// some lanes skip from being moved across.
+__device__ __forceinline__ void rg_wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+constexpr int rg_lcm(int a, int b) {
+    int m = a;
+    while (m % b) m += a;
+    return m;
+}
+
+#if DT == 3
+// The tile's outputs by plain fp32 fused multiply-adds from the filters as
+// they are: for the rare tile whose values the bf16 parts cannot hold.
+__device__ __forceinline__ void slow_tile(const float* __restrict__ Ib, const float* __restrict__ Wr,
+                                                    float* __restrict__ Ob, const int oi0, const int oj0,
+                                                    const int c0) {
+#pragma unroll 1
+    for (int e = threadIdx.x; e < TH * TWO * CB; e += NTHREADS) {
+        const int oj = oj0 + e % TWO, oi = oi0 + e / TWO % TH, c = c0 + e / (TWO * TH);
+        if (oi >= HO || oj >= WO || c >= COUT) continue;
+        float val = 0.f;
+#pragma unroll 1
+        for (int u = 0; u < FH; ++u)
+#pragma unroll 1
+            for (int v = 0; v < FW; ++v) {
+                const int ii = oi + u - PADH, jj = oj + v - PADW;
+                if (ii < 0 || ii >= HI || jj < 0 || jj >= WI) continue;
+#pragma unroll 1
+                for (int k = 0; k < CIN; ++k)
+#ifdef FB_FLIP
+                    val = fmaf(Ib[((long)ii * WI + jj) * CIN + k],
+                               Wr[(((long)k * FH + (FH - 1 - u)) * FW + (FW - 1 - v)) * COUT + c], val);
+#else
+                    val = fmaf(Ib[((long)ii * WI + jj) * CIN + k], Wr[(((long)c * FH + u) * FW + v) * CIN + k], val);
 #endif
-    const int tx = lin % ntx;
-    const int ty = (lin / ntx) % nty;
-    const int cblk = (lin / (ntx * nty)) % ncb;
-    const int b = lin / (ntx * nty * ncb);
-    const int oi0 = ty * TH, oj0 = tx * TWO, c0 = cblk * CB;
-    const float* Ib = I + (long)b * HI * WI * CIN;
+            }
+#ifdef FB_EPILOGUE
+        val = FB_EPILOGUE(val, c);
+#endif
+        Ob[((long)oi * WO + oj) * COUT + c] = val;
+    }
+}
+#endif
 
+// One output tile: rows oi0.., columns oj0.., column block cblk.  I and O
+// point at the image's input and output, Bp at its packed bank, UNSCALE at
+// the bank's column scales, Wr at the filters themselves.
+__device__ __forceinline__ void rgemm_body(
+    const float* __restrict__ Ib, const rg_u32x4* __restrict__ Bp, const float* __restrict__ UNSCALE,
+    const float* __restrict__ Wr, float* __restrict__ Ob, const int oi0, const int oj0, const int cblk,
+    rg_u32x4* __restrict__ lds)
+{
+    const int c0 = cblk * CB;
+    rg_unit* const tile = (rg_unit*)lds;
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WM, wn = wave / WM;
     const int lr = lane % MF, g = lane / MF;       // tile row (pixel) / lane group
     const int ti = lr / MC, tj = lr % MC;
-    // this lane's first cell (step 0, filter row 0, pixel tile 0)
-    const int lb = RUN_PLANE(g * PE) * PLANE + (wm * MT * MR + ti) * TCP + S * tj + RUN_TAP(g * PE);
-    // this wave's first column tile of the packed bank; column tiles are
-    // NCHUNK*KSTEPS2 kilobyte blocks apart (the bank has whole column
-    // blocks, so every tile a wave names exists)
+    // Unit offset of cell c of the chunk from a pixel's first cell.
+    auto cell_off = [](const int c) -> int {
+        const int u = c / CPR, cc = c % CPR;
+#if LIN
+        return u * RSU + cc * 2;
+#else
+        return u * RSU + (cc % NPL) * PLANE + COLPOS(cc / NPL);
+#endif
+    };
+    // this lane's first pixel (pixel tile 0), and its group's share of an
+    // offset when the groups differ by a constant
+    const int lp = (wm * MT * MR + ti) * RSU + tj * LSTEP;
+    const int lb = SEP ? lp + (g == 0 ? 0 : g == 1 ? cell_off(1) : g == 2 ? cell_off(2) : cell_off(3)) : lp;
+    // offset of this lane's cell of step t; cells from lim on (the padding of
+    // the last step) read cell lim - 1 instead
+    auto step_off = [&](const int t, const int lim) -> int {
+        const int o = cell_off(NKG * t);
+        if (SEP) return o;
+        auto off = [&](const int k) { return cell_off(NKG * t + k < lim ? NKG * t + k : lim - 1) - o; };
+        return o + (g == 0 ? 0 : g == 1 ? off(1) : g == 2 ? off(2) : off(3));
+    };
+    // this wave's first column tile of the packed bank (which has whole
+    // column blocks, so every tile a wave names exists)
     const int j0 = cblk * (NCOLW / MF) + wn * NT;
-    const rg_u32x4* bw = Bp + (long)j0 * NCHUNK * KSTEPS2 * 64 + lane;
+    const long jst = (long)NCHUNK * KSTEPS2 * NSP * 64;     // cells per column tile
+    const rg_u32x4* bw = Bp + j0 * jst;                     // the same in every lane
+    const unsigned boff = lane * 16;
+    auto load_b = [&](const rg_u32x4* p) { return *(const rg_u32x4*)((const char*)p + boff); };
 
-    rg_acc acc[MT][NT];
+    rg_acc acc[MT][NT][NACC];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-            for (int r = 0; r < NREG; ++r) acc[mt][nt][r] = 0.f;
+            for (int k = 0; k < NACC; ++k)
+#pragma unroll
+                for (int r = 0; r < NREG; ++r) acc[mt][nt][k][r] = 0.f;
 
     // fp16: per-tensor input scale 2^-kx (1 unless the input reaches 2^15)
 #if DT == 2
@@ -458,119 +678,183 @@ FB_KNAME(const float* __restrict__ I, const rg_u32x4* __restrict__ Bp, const flo
 #else
     const float xs = 1.f, ys = 1.f;
 #endif
-    (void)ys;
+    (void)ys; (void)Wr;
+#if DT == 3
+    // a column of this block with a non-finite filter, or (below) a staged
+    // value that the parts cannot hold
+    bool odd = false;
+    for (int i = tid; i < NCOLW; i += NTHREADS) odd = odd || UNSCALE[cblk * NCOLW + i] == 0.f;
+#endif
 
 #pragma unroll 1
     for (int kci = 0; kci < NCHUNK; ++kci) {
-        const rg_u32x4* bc = bw + (long)kci * KSTEPS2 * 64;
-        rg_u32x4 bq[PF][NT];
+        const rg_u32x4* bc = bw + (long)kci * KSTEPS2 * NSP * 64;
+        rg_u32x4 bq[PF][NT][NSP];
         // the first PF steps' fragments are in flight while the tile is staged
 #pragma unroll
         for (int r = 0; r < PF; ++r)
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
-                bq[r][nt] = bc[((long)nt * NCHUNK * KSTEPS2 + r) * 64];
+#pragma unroll
+                for (int p = 0; p < NSP; ++p) bq[r][nt][p] = load_b(bc + nt * jst + (r * NSP + p) * 64);
         if (kci > 0) __syncthreads();        // every wave is done with the previous chunk
-        // Stage the chunk's input tile: cell (plane p, row r, column cc) =
-        // channels kci*KC + p*PE .. +PE-1 of input pixel (oi0+r-PADH,
-        // oj0+cc-PADW); zero outside the image and past CIN.  In batches of
-        // SB cells per thread, every load of a batch issued before the
-        // first conversion (one memory latency per batch, not per cell).
+        // Stage the chunk's input tile: ITEM channels of input pixel
+        // (oi0+r-PADH, oj0+cc-PADW) per item; zero outside the image and
+        // past CIN.  In batches of SB items per thread, every load of a
+        // batch issued before the first conversion (one memory latency per
+        // batch, not per item).
+        RgRange range;
 #pragma unroll 1
-        for (int e0 = 0; e0 < NPL * TR * TC; e0 += SB * NTHREADS) {
-            float v[SB][PE];
+        for (int e0 = 0; e0 < SITEMS; e0 += SB * NTHREADS) {
+            float v[SB][ITEM];
+            // item e: tile row r, column cc, channels kci*KC + q0..; its unit
+            auto item = [&](const int e, int& r, int& cc, int& q0) -> int {
+#if LIN
+                const int q = e % ROWU;
+                r = e / ROWU; cc = q * 4 / KC; q0 = q * 4 % KC;
+                return r * RSU + q;
+#else
+                const int rc = e / NPL, p = e % NPL;
+                cc = rc % TC; r = rc / TC; q0 = p * PE;
+                return (p * TR + r) * RSU + COLPOS(cc);
+#endif
+            };
 #pragma unroll
             for (int i = 0; i < SB; ++i) {
                 const int e = e0 + i * NTHREADS + tid;
-                const int p = e % NPL;
-                const int rc = e / NPL;
-                const int cc = rc % TC, r = rc / TC;
+                int r, cc, q0;
+                item(e, r, cc, q0);
                 const int ii = oi0 + r - PADH, jj = oj0 + cc - PADW;
-                const int ch = kci * KC + p * PE;
-                const bool in = e < NPL * TR * TC && ii >= 0 && ii < HI && jj >= 0 && jj < WI;
+                const int ch = kci * KC + q0;
+                const bool in = e < SITEMS && ii >= 0 && ii < HI && jj >= 0 && jj < WI;
                 const float* src = Ib + ((long)ii * WI + jj) * CIN + ch;
-#if CIN % PE == 0
-                if (in && ch < CIN) {
+#if KC % 4 != 0
+                // an item may straddle pixels (of whole image rows in memory)
 #pragma unroll
-                    for (int q = 0; q < PE; q += 4) {
-                        const rg_f32x4 x4 = *(const rg_f32x4*)(src + q);
-                        v[i][q] = x4[0]; v[i][q + 1] = x4[1]; v[i][q + 2] = x4[2]; v[i][q + 3] = x4[3];
-                    }
-                } else {
+                for (int q = 0; q < ITEM; ++q) {
+                    const int j2 = jj + (q0 + q) / KC;
+                    v[i][q] = (e < SITEMS && ii >= 0 && ii < HI && j2 >= 0 && j2 < WI) ? src[q] : 0.f;
+                }
+                (void)in;
+#elif CIN % 4 == 0
 #pragma unroll
-                    for (int q = 0; q < PE; ++q) v[i][q] = 0.f;
+                for (int q = 0; q < ITEM; q += 4) {
+                    rg_f32x4 x4 = {0.f, 0.f, 0.f, 0.f};
+                    if (in && ch + q < CIN) x4 = *(const rg_f32x4*)(src + q);
+                    v[i][q] = x4[0]; v[i][q + 1] = x4[1]; v[i][q + 2] = x4[2]; v[i][q + 3] = x4[3];
                 }
 #else
 #pragma unroll
-                for (int q = 0; q < PE; ++q) v[i][q] = (in && ch + q < CIN) ? src[q] : 0.f;
+                for (int q = 0; q < ITEM; ++q) v[i][q] = (in && ch + q < CIN) ? src[q] : 0.f;
 #endif
             }
 #pragma unroll
             for (int i = 0; i < SB; ++i) {
                 const int e = e0 + i * NTHREADS + tid;
-                const int p = e % NPL;
-                const int rc = e / NPL;
-                const int cc = rc % TC, r = rc / TC;
-                if (e < NPL * TR * TC) tile[(p * TR + r) * TCP + cc] = rg_cell(v[i], xs);
+                int r, cc, q0;
+                const int dst = item(e, r, cc, q0);
+                if (e < SITEMS) rg_put(tile + dst, v[i], xs, range);
             }
         }
+#if DT == 3
+        odd = odd || range.outside();
+#endif
         __syncthreads();
 
-        // cell offset of step s relative to the lane's first cell
-        auto step_off = [](int s) -> int {
-            const int u = s / NSTEP, t = s % NSTEP;
-            return RUN_PLANE(E * t) * PLANE + RUN_TAP(E * t) + u * TCP;
-        };
         // A fragments one step ahead of the products that use them
-        rg_u32x4 a[2][MT];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) a[0][mt] = tile[lb + mt * MR * TCP];
-
-        // One step: read the next step's A fragments, the products of this
-        // one, then refill this ring slot with the fragments PF steps ahead
-        // (the packed bank has PF zero steps after each chunk, so the refill
-        // needs no bounds test; nor does the A read, whose step is clamped).
-        auto step = [&](const int s, const int r, const int ab) {
-            const int sn = s + 1 < KSTEPS ? s + 1 : KSTEPS - 1;
-            const int so = step_off(sn);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) a[ab ^ 1][mt] = tile[lb + so + mt * MR * TCP];
+        rg_u32x4 a[2][MT][NSP];
+        auto read_a = [&](const int base, const int t, const int lim, rg_u32x4 (&dst)[MT][NSP]) {
+            const int o = lb + base + step_off(t, lim);
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) rg_mma(acc[mt][nt], a[ab][mt], bq[r][nt]);
+                for (int p = 0; p < NSP; ++p) dst[mt][p] = rg_read(tile, o + mt * MR * RSU + p * SPU);
+        };
+        read_a(0, 0, NCELL, a[0]);
+
+        // One step: read the next step's A fragments (step tn past unit
+        // offset base, lim cells left there), the products of this one, then refill this ring slot
+        // with the fragments PF steps ahead (the packed bank has PF zero
+        // steps after each chunk, so the refill needs no bounds test).
+        auto step = [&](const int base, const int tn, const int lim, const rg_u32x4* brow, const int r, const int ab) {
+            read_a(base, tn, lim, a[ab ^ 1]);
+#if DT == 3
+            // the small products first; neighbouring instructions on
+            // different tiles
+            constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) bq[r][nt] = bc[((long)nt * NCHUNK * KSTEPS2 + s + PF) * 64];
+            for (int q = 0; q < 6; ++q)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+                        rg_mma(acc[mt][nt][q < 5], a[ab][mt][PA[q]], bq[r][nt][PB[q]]);
+#else
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) rg_mma(acc[mt][nt][0], a[ab][mt][0], bq[r][nt][0]);
+#endif
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int p = 0; p < NSP; ++p) bq[r][nt][p] = load_b(brow + nt * jst + (PF * NSP + p) * 64);
             // Keep this order (LDS reads, products, refill loads) and keep
             // each step's instructions within the step: left free, the
             // scheduler sinks the refills next to their use, which leaves
             // the ring one step deep.
-            __builtin_amdgcn_sched_group_barrier(0x100, MT, 0);        // LDS reads
-            __builtin_amdgcn_sched_group_barrier(0x008, MT * NT * (DT == 0 ? 4 : 1), 0);   // products
-            __builtin_amdgcn_sched_group_barrier(0x020, NT, 0);        // global loads
+            __builtin_amdgcn_sched_group_barrier(0x100, MT * NSP, 0);                         // LDS reads
+            __builtin_amdgcn_sched_group_barrier(0x008, MT * NT * (DT == 0 ? 4 : DT == 3 ? 6 : 1), 0);   // products
+            __builtin_amdgcn_sched_group_barrier(0x020, NT * NSP, 0);                         // global loads
             __builtin_amdgcn_sched_barrier(0);
         };
-        // whole groups of 2*PF steps (ring slot and A buffer repeat with
-        // that period), then the remainder, unrolled
-        constexpr int G = 2 * PF;
+        // whole groups of G steps (the ring slot, the A buffer and the
+        // pattern of offsets repeat with that period), then the rest,
+        // unrolled; the last step of all has no next one, and the one before
+        // it reads the padded step
+        constexpr int GL = rg_lcm(PSTEPS, rg_lcm(PF, 2));
+        // (a long period is cut to whole ring turns, its offsets computed)
+        constexpr bool PERIODIC = GL <= 64;
+        constexpr int G = PERIODIC ? GL : rg_lcm(PF, 2);
+        constexpr int NG = (KSTEPS - (NCELL % NKG ? 2 : 1)) / G;
+        int base = 0;
 #if defined(FB_UNR) && FB_UNR
 #pragma unroll
 #else
 #pragma unroll 1
 #endif
-        for (int base = 0; base < KSTEPS / G * G; base += G) {
+        for (int gi = 0; gi < NG; ++gi) {
+            const rg_u32x4* bg = bc + (long)gi * G * NSP * 64;
+            const int t0 = PERIODIC ? 0 : gi * G;
 #pragma unroll
-            for (int r2 = 0; r2 < G; ++r2) step(base + r2, r2 % PF, r2 & 1);
+            for (int r2 = 0; r2 < G; ++r2) step(base, t0 + r2 + 1, NCELL, bg + r2 * NSP * 64, r2 % PF, r2 & 1);
+            if (PERIODIC) base += G / PSTEPS * PROWS * RSU;
         }
+        constexpr int REST = KSTEPS - NG * G;
+        const rg_u32x4* br = bc + (long)NG * G * NSP * 64;
+        const int tr0 = PERIODIC ? 0 : NG * G, lim = PERIODIC ? NCELL - NG * G * NKG : NCELL;
 #pragma unroll
-        for (int r2 = 0; r2 < KSTEPS % G; ++r2) step(KSTEPS / G * G + r2, r2 % PF, r2 & 1);
+        for (int r2 = 0; r2 < REST; ++r2)
+            step(base, tr0 + (r2 + 1 < REST ? r2 + 1 : r2), lim, br + r2 * NSP * 64, r2 % PF, r2 & 1);
     }
+#if DT == 3
+    // (the same decision in every wave of the workgroup)
+    if (__builtin_amdgcn_readfirstlane(__syncthreads_or(odd))) {
+        slow_tile(Ib, Wr, Ob, oi0, oj0, c0);
+        return;
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int r = 0; r < NREG; ++r) acc[mt][nt][0][r] += acc[mt][nt][1][r];
+#endif
 
     // Epilogue.  Accumulator layouts: 32x32 -- lane l, register r holds tile
     // row 8*(r/4) + 4*(l/32) + r%4 and column l%32; 16x16 -- row 4*(l/16) + r
     // and column l%16.  Workgroups whose tile lies inside the output store
     // without per-element bounds tests.
-    float* const Ob = O + (long)b * HO * WO * COUT;
     const bool interior = oi0 + TH <= HO && oj0 + TWO <= WO && c0 + CB <= COUT;
     auto store_all = [&](auto checked) {
 #pragma unroll
@@ -593,9 +877,9 @@ FB_KNAME(const float* __restrict__ I, const rg_u32x4* __restrict__ Bp, const flo
                     const int oj = oj0 + S * (m % MC) + sh;
                     if (!decltype(checked)::value || (oi < HO && oj < WO && cc < COUT)) {
 #if DT == 0
-                        float val = acc[mt][nt][r];
+                        float val = acc[mt][nt][0][r];
 #else
-                        float val = acc[mt][nt][r] * us;
+                        float val = acc[mt][nt][0][r] * us;
 #endif
 #ifdef FB_EPILOGUE
                         val = FB_EPILOGUE(val, cc);
@@ -625,7 +909,7 @@ FB_KNAME(const float* __restrict__ I, const rg_u32x4* __restrict__ Bp, const flo
         // channel of the column block exists (COUT is a multiple of 4);
         // pixels past the image edge are skipped per vector.
         __syncthreads();
-        float* const sbuf = (float*)tile + wave * SWAVE;
+        float* const sbuf = (float*)lds + wave * SWAVE;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
@@ -642,16 +926,21 @@ FB_KNAME(const float* __restrict__ I, const rg_u32x4* __restrict__ Bp, const flo
                     const int m = 4 * g + r;
 #endif
 #if DT == 0
-                    float val = acc[mt][nt][r];
+                    float val = acc[mt][nt][0][r];
 #else
-                    float val = acc[mt][nt][r] * us;
+                    float val = acc[mt][nt][0][r] * us;
 #endif
 #ifdef FB_EPILOGUE
-                    val = FB_EPILOGUE(val, c0 + col);
+                    const int ch = c0 + col;      // (the macro's argument is used as it is)
+                    val = FB_EPILOGUE(val, ch);
 #endif
                     sbuf[m * SROW + nt * MF + lr] = val;
                 }
             }
+            // (the rows are exchanged between the lanes of the wave: every
+            // lane's writes come before any lane's reads, and those before
+            // the next tile's writes)
+            rg_wave_sync();
             // MF rows of NT*MF/4 vectors, 64 per instruction
 #pragma unroll
             for (int it = lane; it < MF * NT * MF / 4; it += 64) {
@@ -669,6 +958,7 @@ FB_KNAME(const float* __restrict__ I, const rg_u32x4* __restrict__ Bp, const flo
 #endif
                 }
             }
+            rg_wave_sync();
         }
     } else {
         store_all(RgBool<true>{});
@@ -677,5 +967,30 @@ FB_KNAME(const float* __restrict__ I, const rg_u32x4* __restrict__ Bp, const flo
     if (interior) store_all(RgBool<false>{});
     else store_all(RgBool<true>{});
 #endif
+}
+
+extern "C" __global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
+FB_KNAME(const float* __restrict__ I, const rg_u32x4* __restrict__ Bp, const float* __restrict__ UNSCALE,
+         float* __restrict__ O, const float* __restrict__ Wr)
+{
+    __shared__ rg_u32x4 lds[LDS_CELLS];
+    // Workgroup -> (image, column block, tile row, tile column); with XCDMAP
+    // each XCD gets a contiguous range (shared halos stay in its L2).
+    const int ntx = (WO + TWO - 1) / TWO;
+    const int nty = (HO + TH - 1) / TH;
+    const int ncb = (COUT + CB - 1) / CB;
+    const int total = ntx * nty * ncb * BATCH;
+    int lin = blockIdx.x;
+#if FB_XCDMAP
+    {
+        const int q = total / 8, r = total % 8, x = lin % 8;
+        lin = x * q + (x < r ? x : r) + lin / 8;
+    }
+#endif
+    const int tx = lin % ntx;
+    const int ty = (lin / ntx) % nty;
+    const int cblk = (lin / (ntx * nty)) % ncb;
+    const int b = lin / (ntx * nty * ncb);
+    rgemm_body(I + (long)b * HI * WI * CIN, Bp, UNSCALE, Wr, O + (long)b * HO * WO * COUT, ty * TH, tx * TWO, cblk, lds);
 }
 #endif  // !FB_PACK_FRAG

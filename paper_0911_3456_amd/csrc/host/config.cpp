@@ -149,7 +149,7 @@ static const TilePrices kSplitPrices = {3.293e-4, 1.535e-4, 5.901e-5, 2.977e-5, 
 // 16-bit operands: 1230 timings over 14 problems, error 14 %, choice 10 %
 // behind the fastest of about 85 tilings.
 static const TilePrices kLowpPrices = {4.676e-4, 1.435e-4, 3.716e-5, 8.939e-5, 1.729e-4, 1.736e-4,
-                                       2.166e-5, 5.877e-3, 5.469e-4, 0.0,      8.826e-4, 6.493e-3,
+                                       2.166e-5, 5.877e-3, 5.469e-4, 0.0,      8.826e-4, 9.000e-3,
                                        7.279e-4, 0.9402,   0.0,      0.0,      8.339};
 
 struct Tiling {
@@ -165,6 +165,11 @@ static double price_tiling(const Tiling& c, const CorrProblem& p, int nsp, const
     if (regs > 256) return 1e30;
     const int ho = p.hi + 2 * p.padh - p.fh + 1, wo = p.wi + 2 * p.padw - p.fw + 1;
     const int cpr = cdiv((p.fw + c.s - 1) * c.kc, 8), nch = cdiv(p.cin, c.kc), ks = cdiv(p.fh * cpr, nkg);
+    // More than 64 stored values per lane after few steps, or in plain stores:
+    // a wave's stores have nothing to run beside (3 x 3 windows: 4 x 2 tiles
+    // of 32 in plain stores 25 us, 2 x 2 tiles 18; with 4 channels, through
+    // LDS, 20.0 us, 2 x 1 tiles 17.0).
+    if ((!c.ste || ks * nch < 8) && c.mt * c.nt * (c.mf * c.mf / 64) > 64) return 1e30;
     const int mc = c.mf / c.mr, th = c.wm * c.mt * c.mr, two = c.s * mc, cb = c.wn * c.nt * c.mf / c.s;
     const int tr = th + p.fh - 1, tc = c.s * (mc - 1) + cdiv(cpr * 8, c.kc);
     long lds = nsp * (planes ? (long)npl * tr * cdiv(tc, c.s) * c.s * 16
@@ -188,7 +193,9 @@ static double price_tiling(const Tiling& c, const CorrProblem& p, int nsp, const
     double t = pr.call + tm * (pr.mfma + (c.mf == 32 ? pr.mfma32 : 0.0) + pr.mfma1 * std::max(0.0, 2.0 - per_simd));
     t += tl * (pr.lds + (planes ? 0.0 : pr.ldslin)) + tb * (pr.b + pr.bwg * c.wn / w);
     t += qe * st * (pr.stage + (c.mr > 2 ? pr.stage_rows : 0.0) + pr.stage_alone / cc);
-    t += te * (pr.store + (c.ste ? 0.0 : pr.store_plain) + (c.nts ? 0.0 : pr.store_cached));
+    // plain stores: a row of 32 columns is a whole line, one of 16 half of one
+    t += te * (pr.store + (c.ste ? 0.0 : pr.store_plain * (c.mf == 32 ? 0.75 : 1.0)) +
+               (c.nts ? 0.0 : pr.store_cached));
     return t + seq * (nch * pr.chunk + steps * pr.step + mfma * pr.chain);
 }
 
@@ -209,7 +216,8 @@ static Config cheapest_rgemm(const CorrProblem& p, int nsp) {
     c.pf = nsp == 3 ? 2 : 4;
     // Streaming stores leave L2 to the operands; an output that L2 can hold
     // (8 x 4 MB) is stored through it, for the kernel that reads it next.
-    c.nts = (double)p.batch * ho * wo * cout * 4 > 32.0 * (1 << 20) ? 1 : 0;
+    // Only whole 16-byte stores stream: 4-byte ones need L2 to become lines.
+    const bool past_l2 = (double)p.batch * ho * wo * cout * 4 > 32.0 * (1 << 20);
     double best_t = 1e30;
     for (int kc : kcs)
         for (int mf : {16, 32})
@@ -223,6 +231,7 @@ static Config cheapest_rgemm(const CorrProblem& p, int nsp) {
                 if (s == 8 && cout > 8) continue;
                 c.kc = kc; c.mf = mf; c.s = s;
                 c.ste = s == 1 && cout % 4 == 0 ? 1 : 0;
+                c.nts = past_l2 && c.ste;
                 const int need = cdiv(cout * s, mf) * mf / s;        // filters that can be used
                 for (c.wn = 1; c.wn <= 4; ++c.wn)
                     for (c.nt = 1; c.nt <= 4; ++c.nt) {

@@ -45,6 +45,10 @@ CHECK_DEFINES = {
                "-DFB_RH=2 -DFB_RW=32 -DFB_NW=8 -DFB_TPB=21 -DFB_NP=128 -DFB_GPAD=4 -DFB_XPAD=4 -DFB_PF=1",
                "-DFB_BATCH=1 -DFB_FH=9 -DFB_FW=9 -DFB_D=8 -DFB_N=64 -DFB_H=256 -DFB_W=256 -DFB_HO=248 -DFB_WO=248 "
                "-DFB_RH=2 -DFB_RW=64 -DFB_NW=8 -DFB_TPB=21 -DFB_NP=128 -DFB_GPAD=4 -DFB_XPAD=4 -DFB_PF=2"],
+    "dws.hip": ["-DFB_BATCH=32 -DFB_FH=7 -DFB_FW=7 -DFB_D=16 -DFB_N=64 -DFB_H=128 -DFB_W=128 -DFB_HO=122 -DFB_WO=122 "
+                "-DFB_RT=2 -DFB_NW=8 -DFB_NCB=1 -DFB_RH=1 -DFB_RW=64 -DFB_RSEG=61 -DFB_NP=128",
+                "-DFB_BATCH=2 -DFB_FH=5 -DFB_FW=3 -DFB_D=3 -DFB_N=40 -DFB_H=40 -DFB_W=50 -DFB_HO=36 -DFB_WO=48 "
+                "-DFB_RT=3 -DFB_NW=4 -DFB_NCB=1 -DFB_RH=2 -DFB_RW=48 -DFB_RSEG=9 -DFB_NP=8"],
     "nn.hip": ["-DFB_NN_NORMS -DFB_NN_OFFSETS -DFB_NN_SCATTER -DFB_T=4096 -DFB_M=1048576 -DFB_D=64 -DFB_SPLIT=1",
                "-DFB_NN_NORMS -DFB_T=4096 -DFB_M=4096 -DFB_D=64 -DFB_SPLIT=0",
                "-DFB_NN_SCAN -DFB_T=4096 -DFB_M=1048576 -DFB_D=64 -DFB_SPLIT=1 -DFB_NT=8 -DFB_WV=4 -DFB_CH=128 "

@@ -49,6 +49,9 @@ bool tuning_db_record_key(const std::string& key, const std::string& cfg, std::s
 Config default_igemm(int cin, int cout, bool lowp);
 Config default_rgemm(int cin, int cout, bool lowp);
 Config default_direct(const fbcorr_desc& d);
+Config default_dw(const fbcorr_desc& d, int cus);
+// The cheapest `count` three-part filter-gradient tilings, cheapest first.
+std::vector<Config> dws_tilings(const fbcorr_desc& d, int cus, int count);
 // The configuration a text such as "algo=rgemm mt=2" describes for a role:
 // unnamed knobs come from the role's default, or from the named algorithm's
 // hand-written defaults when it differs from the default's (always, on the

@@ -234,7 +234,7 @@ std::vector<Config> tune_candidates(const fbcorr_desc& d, int role, bool with_di
                                     }
         }
     } else {
-        const Config base = default_config(d, role, DeviceInfo{"gfx950", 256, 160 * 1024, 1024});
+        const Config base = default_dw(d, 256);
         const int tiles = ((d.N + 31) / 32) * ((d.fh * d.fw * d.D + 31) / 32);
         std::vector<Config> grid;
         // chunk widths: powers of two, and the widths that cut the output
@@ -284,8 +284,13 @@ std::vector<Config> tune_candidates(const fbcorr_desc& d, int role, bool with_di
             st = st * 6364136223846793005ull + 1442695040888963407ull;
             std::swap(grid[i - 1], grid[(st >> 33) % i]);
         }
+        // three-part tilings, cheapest first by the cost model, interleaved
+        const std::vector<Config> parts = dws_tilings(d, 256, 400);
         add(out, seen, base);
-        for (auto& c : grid) add(out, seen, c);
+        for (size_t i = 0; i < std::max(grid.size(), parts.size()); ++i) {
+            if (i < parts.size()) add(out, seen, parts[i]);
+            if (i < grid.size()) add(out, seen, grid[i]);
+        }
     }
     return out;
 }

@@ -9,7 +9,7 @@
 //   <arch> nearest u8 <T> <M> <D> : <config text>      (nearest-neighbour search)
 //
 // A forward entry for the direct kernel carries "direct" after the sizes.  So
-// may an entry carry "igemm" or "rgemm": the tuned configuration of that form
+// may an entry carry "igemm", "rgemm" or "dw": the tuned configuration of that form
 // for a problem whose default is another; it gives the knobs that a
 // configuration text naming the form leaves out.
 //

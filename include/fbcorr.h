@@ -225,7 +225,7 @@ FBCORR_API fbcorr_status fbcorr_tune(fbcorr_plan_t plan, const float* x, const f
 /* ---- many uneven images in one launch ----------------------------------
  * fbcorr_plan_batched: `count` independent problems (each desc has batch 1,
  * its own H, W, D, N, fh, fw and its own filter bank; FP32 only).  One
- * persistent kernel is generated holding exactly the variants the distinct
+ * batched kernel is generated holding exactly the variants the distinct
  * (fh, fw, D, N) keys need (Sec. 4.2: code for exactly one purpose); a work
  * table of tiles sorted by cost is built at plan time. */
 FBCORR_API fbcorr_status fbcorr_plan_batched(int32_t count, const fbcorr_desc* descs, int device,
@@ -274,7 +274,7 @@ FBCORR_API fbcorr_status fbcorr_plan_set_epilogue(fbcorr_plan_t plan, const char
  * they are launched on, and accumulates the elapsed time when
  * fbcorr_plan_read_timing is called (which synchronises the events).
  * ms[role] = total milliseconds, calls[role] = role executions.  A batched
- * plan records role 0 around its persistent kernel (eager launches) or its
+ * plan records role 0 around its batched kernel (eager launches) or its
  * graph launch. */
 FBCORR_API fbcorr_status fbcorr_plan_enable_timing(fbcorr_plan_t plan, int enable);
 FBCORR_API fbcorr_status fbcorr_plan_read_timing(fbcorr_plan_t plan, double* ms, int64_t* calls, int reset);
@@ -290,7 +290,7 @@ FBCORR_API fbcorr_status fbcorr_codegen(const fbcorr_desc* desc, int role, const
 FBCORR_API fbcorr_status fbcorr_compile_check(const fbcorr_desc* desc, int role, const char* cfg,
                                    const char* arch, size_t* code_bytes);
 
-/* Generate and compile the persistent batched kernel for `count`
+/* Generate and compile the batched kernel for `count`
  * descriptors (as fbcorr_plan_batched would) for an architecture name,
  * without a device.  Host-only. */
 FBCORR_API fbcorr_status fbcorr_compile_check_batched(int32_t count, const fbcorr_desc* descs, const char* arch,

@@ -176,7 +176,7 @@ def compile_check(desc: Desc, role: str = "forward", cfg: str | None = None, arc
 
 
 def compile_check_batched(descs, arch: str = "gfx950") -> int:
-    """Generate and compile the persistent batched kernel for a list of
+    """Generate and compile the batched kernel for a list of
     descriptors without a device."""
     lib = load()
     arr = (Desc * len(descs))(*descs)

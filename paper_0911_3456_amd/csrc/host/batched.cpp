@@ -1,16 +1,23 @@
-// Many uneven images in one persistent launch.
+// Many uneven images in one launch.
 //
 // Every distinct problem key (fh, fw, D, N) of the batch gets one tile
 // configuration, and the generator emits one kernel holding exactly those
-// variants (Sec. 4.2: generate code for exactly one purpose): the
-// implicit-GEMM body section is pasted once per key with that key's constants
-// substituted and the image extents left run-time, followed by a dispatch
-// loop.  Each body stays a function of its own (not inlined into the loop),
-// so registers are allocated per variant.  At plan time the host builds a work table of (variant, image, tile)
-// items sorted by cost, largest first; at run time each persistent
-// workgroup takes the next item from an integer counter until the table is
-// exhausted.  The launch (a counter-reset kernel plus the persistent kernel)
-// can be captured once into a HIP graph per stream and replayed.
+// variants (Sec. 4.2: generate code for exactly one purpose): the body
+// section of the key's kernel -- fp32 operands as three bf16 parts (rgemm),
+// or fp32 instructions (igemm) -- is pasted once per key with that key's
+// constants substituted and the image extents left run-time.  Each body stays
+// a function of its own, so registers are allocated per variant.  At plan
+// time the host builds a work table of (variant, image, tile) items sorted by
+// cost, largest first; each workgroup runs one.  Before it, one launch packs
+// the banks of the images whose variant is an rgemm, one workgroup per
+// column.  Both launches can be captured once into a HIP graph per stream and
+// replayed.
+//
+// One workgroup per item, not workgroups that loop over a counter: a wave
+// that ends does not wait for its stores, one that takes another tile waits
+// for them at its next load, and two workgroups per CU do not hide that (32
+// images of 96 to 512 pixels a side, 365 GFLOP, three-part variants: 2115 us
+// looping, 1590 us so; with fp32 instructions 3553 and 3390 us).
 #include "plan.h"
 
 #include <algorithm>
@@ -26,6 +33,9 @@ struct BVariant {
     Config cfg;
     int th, two, cb;       // tile geometry: output rows, columns, channels
     int lds;
+    int ncols = 0;         // rgemm: columns of a packed bank, and its bytes
+    size_t bank = 0;
+    bool parts() const { return cfg.algo == "rgemm"; }
     // the -DFB_<name>[=<value>] options build_role generated for this key's
     // standalone kernel (clamped and completed exactly as that kernel was)
     std::vector<std::string> opts;
@@ -36,10 +46,13 @@ struct BatchedState {
     std::vector<BVariant> vars;
     std::vector<int> img_var;
     std::vector<int32_t> items;     // 4 ints per item: variant, image, tile, 0
-    std::vector<int32_t> imgs;      // 4 ints per image: H, W, Ho, Wo
-    Kernel kernel, reset;
+    // 8 ints per image: H, W, Ho, Wo, then (rgemm) where its packed bank and
+    // its column scales start in the workspace, in units of 256 bytes
+    std::vector<int32_t> imgs;
+    std::vector<int32_t> cols;      // 4 ints per packed column: variant, image, column, 0
+    Kernel kernel, pack;
     int grid = 0, threads = 256, per_cu = 1;
-    size_t off_counter = 0, off_items = 0, off_imgs = 0, ws_bytes = 0;
+    size_t off_items = 0, off_imgs = 0, off_cols = 0, ws_bytes = 0;
     int64_t nitems = 0;
     double flops = 0;
     std::string source_desc;
@@ -60,7 +73,8 @@ struct BatchedState {
 static int cdiv(int a, int b) { return (a + b - 1) / b; }
 static size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
-// Four waves per workgroup for every variant (one block size for the launch).
+// fp32 instructions; four waves per workgroup for every variant (one block
+// size for the launch).
 static Config batched_variant_config(int D, int N) {
     Config c = default_igemm(D, N, false);
     const int s = c.get("s");
@@ -98,24 +112,37 @@ static std::vector<std::string> body_macros(const std::string& body) {
     return names;
 }
 
-static bool generate(BatchedState& st, const DeviceInfo& di, KernelSource& ks, std::string& err) {
-    const std::string& tpl = template_source("igemm");
+// The part of a kernel template between its BODY markers, and what precedes it.
+struct Body {
+    std::string header, text;
+    std::vector<std::string> macros;
+};
+
+static bool template_body(const std::string& file, Body& out, std::string& err) {
+    const std::string& tpl = template_source(file);
     const auto b0 = tpl.find("//@@BODY-BEGIN"), b1 = tpl.find("//@@BODY-END");
-    if (b0 == std::string::npos || b1 == std::string::npos) { err = "igemm template lacks body markers"; return false; }
-    const std::string header = tpl.substr(0, b0);
-    const std::string body = tpl.substr(b0, b1 - b0);
-    const std::vector<std::string> macros = body_macros(body);
+    if (b0 == std::string::npos || b1 == std::string::npos) { err = file + " template lacks body markers"; return false; }
+    out.header = tpl.substr(0, b0);
+    out.text = tpl.substr(b0, b1 - b0);
+    out.macros = body_macros(out.text);
+    return true;
+}
+
+static bool generate(BatchedState& st, KernelSource& ks, std::string& err) {
+    Body igemm, rgemm;
+    if (!template_body("igemm", igemm, err) || !template_body("rgemm", rgemm, err)) return false;
     std::ostringstream src;
-    src << "// Generated persistent batched filter-bank correlation: " << st.vars.size() << " variant(s).\n";
-    src << "#define FB_BATCHED 1\n" << header;
+    src << "// Generated batched filter-bank correlation: " << st.vars.size() << " variant(s).\n";
+    src << "#define FB_BATCHED 1\n" << igemm.header << rgemm.header;
     int maxlds = 16;
     // Options of the standalone kernel that do not apply inside the
-    // persistent kernel: its name, the batch, the image extents (run-time
-    // arguments here) and the workgroup order (set by the dispatch loop).
+    // batched kernel: its name, the batch, the image extents (run-time
+    // arguments here) and the workgroup order (the work table).
     static const std::set<std::string> skip = {"FB_KNAME", "FB_BATCH", "FB_HI", "FB_WI", "FB_HO", "FB_WO",
                                                "FB_XCDMAP"};
     for (size_t v = 0; v < st.vars.size(); ++v) {
         const BVariant& bv = st.vars[v];
+        const Body& body = bv.parts() ? rgemm : igemm;
         src << "\n// ---- variant " << v << ": fh=" << bv.fh << " fw=" << bv.fw << " D=" << bv.D << " N=" << bv.N
             << "  [" << bv.cfg.str() << "]\n";
         src << "#undef FB_TAG\n#define FB_TAG v" << v << "\n";
@@ -132,62 +159,82 @@ static bool generate(BatchedState& st, const DeviceInfo& di, KernelSource& ks, s
                 << "\n";
             defined.push_back(name);
         }
-        src << body << "\n";
-        for (auto& m : macros) src << "#undef " << m << "\n";
+        if (bv.parts()) {
+            src << "#define FB_NCOLW (FB_WN * FB_NT * FB_MF)\n";       // as the pack is given it
+            defined.push_back("FB_NCOLW");
+            src << "namespace v" << v << " {\n" << body.text << "\n}\n";
+        } else {
+            src << body.text << "\n";
+        }
+        for (auto& m : body.macros) src << "#undef " << m << "\n";
         for (auto& d : defined) src << "#undef " << d << "\n";
         maxlds = std::max(maxlds, bv.lds);
     }
     src << "\n#define MAXLDS " << ((maxlds + 15) / 16 * 16) << "\n";
     src << R"KSRC(
-// Dispatch: each workgroup takes (variant, image, tile) items from the
-// counter until the table is exhausted; every workgroup then exits.  Two
-// waves per SIMD (registers within 256; every variant's LDS within half a
-// CU): two workgroups per CU.
+// One workgroup per item (variant, image, tile) of the table.  Two waves per
+// SIMD (registers within 256; every variant's LDS within half a CU): two
+// workgroups per CU.
 extern "C" __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
-fbcorr_batched(const int4* __restrict__ items, const int nitems, const int4* __restrict__ imgs,
+fbcorr_batched(const int4* __restrict__ items, const int4* __restrict__ imgs,
                const float* const* __restrict__ xs, const float* const* __restrict__ wts,
-               float* const* __restrict__ ys, int* __restrict__ counter)
+               float* const* __restrict__ ys, const char* __restrict__ ws)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds_raw[MAXLDS];
-    __shared__ int next;
-    for (;;) {
-        if (threadIdx.x == 0) next = atomicAdd(counter, 1);
-        __syncthreads();
-        const int it = next;
-        __syncthreads();
-        if (it >= nitems) break;
-        const int4 w = items[it];
-        const int4 im = imgs[w.y];
-        const float* x = xs[w.y];
-        const float* wt = wts[w.y];
-        float* y = ys[w.y];
-        switch (w.x) {
+    const int4 w = items[blockIdx.x];
+    const int4 im = imgs[2 * w.y], at = imgs[2 * w.y + 1];
+    const float* x = xs[w.y];
+    const float* wt = wts[w.y];
+    float* y = ys[w.y];
+    RG_GLOBAL const rg_u32x4* bank = (RG_GLOBAL const rg_u32x4*)(ws + (size_t)(unsigned)at.x * 256);
+    RG_GLOBAL const float* unscale = (RG_GLOBAL const float*)(ws + (size_t)(unsigned)at.y * 256);
+    (void)bank; (void)unscale;
+    switch (w.x) {
 )KSRC";
     for (size_t v = 0; v < st.vars.size(); ++v) {
         const BVariant& bv = st.vars[v];
-        src << "        case " << v << ": {\n"
-            << "            const int ntx = (im.w + " << bv.two - 1 << ") / " << bv.two << ";\n"
-            << "            const int nty = (im.z + " << bv.th - 1 << ") / " << bv.th << ";\n"
-            << "            const int tx = w.z % ntx, ty = (w.z / ntx) % nty, cb = w.z / (ntx * nty);\n"
-            << "            igemm_body_v" << v << "(x, wt, nullptr, y, im.x, im.y, im.z, im.w, ty * " << bv.th
-            << ", tx * " << bv.two << ", cb * " << bv.cb << ", lds_raw);\n"
-            << "        } break;\n";
+        src << "    case " << v << ":";
+        if (bv.parts())
+            src << " v" << v << "::rgemm_body((RG_GLOBAL const float*)x, bank, unscale, (RG_GLOBAL const float*)wt, "
+                << "(RG_GLOBAL float*)y, im.x, im.y, im.z, im.w, w.z, (RG_LDS rg_u32x4*)lds_raw);\n";
+        else
+            src << " {\n"
+                << "        const int ntx = (im.w + " << bv.two - 1 << ") / " << bv.two << ";\n"
+                << "        const int nty = (im.z + " << bv.th - 1 << ") / " << bv.th << ";\n"
+                << "        const int tx = w.z % ntx, ty = (w.z / ntx) % nty, cb = w.z / (ntx * nty);\n"
+                << "        igemm_body_v" << v << "(x, wt, nullptr, y, im.x, im.y, im.z, im.w, ty * " << bv.th
+                << ", tx * " << bv.two << ", cb * " << bv.cb << ", lds_raw);\n"
+                << "    } break;\n";
     }
-    src << R"KSRC(        default: break;
-        }
+    src << R"KSRC(    default: break;
     }
 }
 
-extern "C" __global__ void __launch_bounds__(64) fbcorr_batched_reset(int* __restrict__ counter)
+// Before it: the packed banks, one workgroup per column of the table.
+extern "C" __global__ void __launch_bounds__(256)
+fbcorr_batched_pack(const int4* __restrict__ cols, const int4* __restrict__ imgs,
+                    const float* const* __restrict__ wts, char* __restrict__ ws)
 {
-    if (threadIdx.x == 0) *counter = 0;
+    __shared__ float red[4];
+    const int4 w = cols[blockIdx.x];
+    const int4 at = imgs[2 * w.y + 1];
+    const float* wt = wts[w.y];
+    RG_GLOBAL rg_u32x4* bank = (RG_GLOBAL rg_u32x4*)(ws + (size_t)(unsigned)at.x * 256);
+    RG_GLOBAL float* unscale = (RG_GLOBAL float*)(ws + (size_t)(unsigned)at.y * 256);
+    (void)wt; (void)bank; (void)unscale;
+    switch (w.x) {
+)KSRC";
+    for (size_t v = 0; v < st.vars.size(); ++v)
+        if (st.vars[v].parts())
+            src << "    case " << v << ": v" << v << "::rg_pack((RG_GLOBAL const float*)wt, bank, unscale, w.z, (RG_LDS float*)red); break;\n";
+    src << R"KSRC(    default: break;
+    }
 }
 )KSRC";
     ks.name = "fbcorr_batched";
     ks.file = "batched";
     ks.source = src.str();
     ks.options.clear();
-    (void)di;
     return true;
 }
 
@@ -226,14 +273,16 @@ static fbcorr_desc variant_key_desc(int fh, int fw, int D, int N) {
 }
 static const int kRoleBatched = 3;
 
-static bool four_waves(const Config& c) {
-    return c.algo == "igemm" && c.get("wm") * c.get("wn") * c.get("ks") == 4;
-}
-
 static fbcorr_status prepare_batched(const DeviceInfo& dev, int32_t count, const fbcorr_desc* descs,
                                      BatchedState* st, KernelSource& ks,
                                      const std::map<KeyT, Config>* overrides = nullptr) {
     std::map<KeyT, int> keyidx;
+    std::map<KeyT, fbcorr_desc> largest;          // of each key, by input pixels
+    for (int32_t i = 0; i < count; ++i) {
+        const fbcorr_desc& d = descs[i];
+        auto l = largest.emplace(std::make_tuple(d.fh, d.fw, d.D, d.N), d).first;
+        if ((double)d.H * d.W > (double)l->second.H * l->second.W) l->second = d;
+    }
     for (int32_t i = 0; i < count; ++i) {
         fbcorr_desc d = descs[i];
         fbcorr_status s0 = validate_desc(&d);
@@ -260,17 +309,27 @@ static fbcorr_status prepare_batched(const DeviceInfo& dev, int32_t count, const
                 tuned = bv.cfg;
                 have = parse_config(text, tuned, err);
             }
-            if (have && four_waves(tuned) && build_role(d, FBCORR_ROLE_FORWARD, tuned, dev, rb, err) &&
-                rb.main_geom.lds <= dev.lds_per_block / 2 - 256) {
+            auto fits = [&](const Config& c) {
+                return build_role(d, FBCORR_ROLE_FORWARD, c, dev, rb, err) && rb.main_geom.lds <= kBatchedLds;
+            };
+            if (have && batched_form(tuned) && fits(tuned)) {
                 bv.cfg = tuned;
                 ok = true;
             }
-            // otherwise the heuristic, shrunk until it fits half a CU's LDS
+            // three bf16 parts, but for windows too short to be anything but
+            // memory traffic (the single plans' line)
+            if (!ok && three_parts_window(d)) {
+                const Config parts = batched_parts(largest[key]);
+                if (batched_form(parts) && fits(parts)) {
+                    bv.cfg = parts;
+                    ok = true;
+                }
+            }
+            // otherwise fp32 instructions, shrunk until they fit half a CU's LDS
             // (the launch's occupancy is set by its largest variant: two
             // workgroups per CU need every variant within half)
             for (int attempt = 0; attempt < 8 && !ok; ++attempt) {
-                ok = build_role(d, FBCORR_ROLE_FORWARD, bv.cfg, dev, rb, err) &&
-                     rb.main_geom.lds <= dev.lds_per_block / 2 - 256;
+                ok = fits(bv.cfg);
                 if (!ok) {
                     if (bv.cfg.v["kc"] > 4) bv.cfg.v["kc"] /= 2;
                     else if (bv.cfg.v["mr"] > 1) bv.cfg.v["mr"] /= 2;
@@ -288,35 +347,68 @@ static fbcorr_status prepare_batched(const DeviceInfo& dev, int32_t count, const
             bv.cb = bv.cfg.get("wn") * bv.cfg.get("nt") * mf / s;
             bv.lds = rb.main_geom.lds;
             bv.opts = rb.main.options;
+            if (bv.parts()) {
+                bv.ncols = rb.aux_geom[0].grid_x;
+                bv.bank = rb.ws_unscale;
+            }
             it = keyidx.emplace(key, (int)st->vars.size()).first;
             st->vars.push_back(bv);
         }
         st->img_var.push_back(it->second);
     }
-    // work table, largest tiles first (stable: image, then tile order)
-    struct Item { double cost; int v, img, tile; };
-    std::vector<Item> items;
+    // Work table, images with the costliest tiles first (stable).  Workgroups
+    // go to the eight XCDs in turn: each XCD takes a contiguous part of an
+    // image's tiles (shared halos stay in its L2), the longest part left once
+    // its own is used up.
     for (int32_t i = 0; i < count; ++i) {
         const fbcorr_desc& d = st->descs[i];
         const BVariant& bv = st->vars[st->img_var[i]];
         const int ho = d.H - d.fh + 1, wo = d.W - d.fw + 1;
-        const int nt = cdiv(wo, bv.two) * cdiv(ho, bv.th) * cdiv(d.N, bv.cb);
-        const double cost = (double)bv.th * bv.two * bv.cb * d.fh * d.fw * d.D;
-        for (int t = 0; t < nt; ++t) items.push_back({cost, st->img_var[i], i, t});
-        st->imgs.insert(st->imgs.end(), {d.H, d.W, ho, wo});
+        st->imgs.insert(st->imgs.end(), {d.H, d.W, ho, wo, 0, 0, 0, 0});
+        for (int c = 0; c < bv.ncols; ++c) st->cols.insert(st->cols.end(), {st->img_var[i], i, c, 0});
         st->flops += 2.0 * ho * wo * d.N * d.fh * d.fw * d.D;
     }
-    std::stable_sort(items.begin(), items.end(), [](const Item& a, const Item& b) { return a.cost > b.cost; });
-    for (auto& it : items) st->items.insert(st->items.end(), {it.v, it.img, it.tile, 0});
-    st->nitems = (int64_t)items.size();
-    FBC_RETURN_IF(st->nitems > 0x7fffffff, FBCORR_ERR_UNSUPPORTED, "too many tiles");
-    // workspace: counter | items | image table
-    st->off_counter = 0;
-    st->off_items = 256;
+    std::vector<int32_t> order(count);
+    std::iota(order.begin(), order.end(), 0);
+    auto tile_cost = [&](int32_t i) {
+        const BVariant& bv = st->vars[st->img_var[i]];
+        // (an operation of the fp32 instructions takes twice as long)
+        return (double)bv.th * bv.two * bv.cb * bv.fh * bv.fw * bv.D * (bv.parts() ? 1 : 2);
+    };
+    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return tile_cost(a) > tile_cost(b); });
+    for (int32_t i : order) {
+        const fbcorr_desc& d = st->descs[i];
+        const BVariant& bv = st->vars[st->img_var[i]];
+        const long nt = (long)cdiv(d.W - d.fw + 1, bv.two) * cdiv(d.H - d.fh + 1, bv.th) * cdiv(d.N, bv.cb);
+        FBC_RETURN_IF(st->items.size() / 4 + nt > 0x7fffffff, FBCORR_ERR_UNSUPPORTED, "too many tiles");
+        long at[8], end[8];
+        for (int x = 0; x < 8; ++x) { at[x] = nt * x / 8; end[x] = nt * (x + 1) / 8; }
+        for (long k = 0; k < nt; ++k) {
+            int x = (int)(st->items.size() / 4 % 8);
+            if (at[x] == end[x])
+                for (int z = 0; z < 8; ++z)
+                    if (end[z] - at[z] > end[x] - at[x]) x = z;
+            st->items.insert(st->items.end(), {st->img_var[i], i, (int32_t)at[x]++, 0});
+        }
+    }
+    st->nitems = (int64_t)(st->items.size() / 4);
+    // workspace: items | image table | column table | packed banks and their
+    // scales
+    st->off_items = 0;
     st->off_imgs = st->off_items + align256(st->items.size() * 4);
-    st->ws_bytes = st->off_imgs + align256(st->imgs.size() * 4);
+    st->off_cols = st->off_imgs + align256(st->imgs.size() * 4);
+    st->ws_bytes = st->off_cols + align256(st->cols.size() * 4);
+    for (int32_t i = 0; i < count; ++i) {
+        const BVariant& bv = st->vars[st->img_var[i]];
+        if (!bv.parts()) continue;
+        st->imgs[8 * i + 4] = (int32_t)(uint32_t)(st->ws_bytes / 256);
+        st->ws_bytes += align256(bv.bank);
+        st->imgs[8 * i + 5] = (int32_t)(uint32_t)(st->ws_bytes / 256);
+        st->ws_bytes += align256((size_t)bv.ncols * 4);
+    }
+    FBC_RETURN_IF(st->ws_bytes / 256 > 0xffffffffull, FBCORR_ERR_UNSUPPORTED, "packed banks too large");
     std::string err;
-    FBC_RETURN_IF(!generate(*st, dev, ks, err), FBCORR_ERR_INTERNAL, err);
+    FBC_RETURN_IF(!generate(*st, ks, err), FBCORR_ERR_INTERNAL, err);
     return FBCORR_OK;
 }
 
@@ -328,15 +420,14 @@ static fbcorr_status build_batched(Plan* p, int32_t count, const fbcorr_desc* de
     s = load_kernel(ks, p->device, st->kernel);
     if (s != FBCORR_OK) return s;
     KernelSource rs = ks;
-    rs.name = "fbcorr_batched_reset";
-    s = load_kernel(rs, p->device, st->reset);
+    rs.name = "fbcorr_batched_pack";
+    s = load_kernel(rs, p->device, st->pack);
     if (s != FBCORR_OK) return s;
     int per_cu = 0;
     hipError_t e = hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, st->kernel.fn, 256, 0);
     if (e != hipSuccess || per_cu < 1) per_cu = 1;
     st->per_cu = per_cu;
-    st->grid = (int)std::min<int64_t>(st->nitems, (int64_t)p->dev.cus * per_cu);
-    st->grid = std::max(st->grid, 1);
+    st->grid = (int)st->nitems;
     p->batch_ws = st->ws_bytes;
     p->bstate = st.release();
     return FBCORR_OK;
@@ -346,14 +437,16 @@ static fbcorr_status launch_batched(Plan* p, const float* const* xs, const float
                                     void* ws, hipStream_t s) {
     BatchedState* st = p->bstate;
     char* base = (char*)ws;
-    int* counter = (int*)(base + st->off_counter);
     const void* items = base + st->off_items;
     const void* imgs = base + st->off_imgs;
-    int nitems = (int)st->nitems;
-    void* a0[] = {&counter};
-    fbcorr_status r = launch(st->reset, LaunchGeom{1, 1, 64, 0}, s, a0);
-    if (r != FBCORR_OK) return r;
-    void* a1[] = {(void*)&items, &nitems, (void*)&imgs, (void*)&xs, (void*)&wts, (void*)&ys, &counter};
+    const void* cols = base + st->off_cols;
+    fbcorr_status r = FBCORR_OK;
+    if (!st->cols.empty()) {
+        void* a0[] = {(void*)&cols, (void*)&imgs, (void*)&wts, &base};
+        r = launch(st->pack, LaunchGeom{(int)(st->cols.size() / 4), 1, 256, 0}, s, a0);
+        if (r != FBCORR_OK) return r;
+    }
+    void* a1[] = {(void*)&items, (void*)&imgs, (void*)&xs, (void*)&wts, (void*)&ys, &base};
     hipEvent_t ev;
     timing_begin(p, FBCORR_ROLE_FORWARD, s, ev);
     r = launch(st->kernel, LaunchGeom{st->grid, 1, 256, 0}, s, a1);
@@ -390,8 +483,8 @@ size_t batched_tune_workspace(const Plan* p) {
 }
 
 // Per-key tuning of a batched plan (Sec. 6.2: the best variant differs per
-// input): each variant is tuned on its largest image among four-wave
-// implicit-GEMM candidates, then the persistent kernel is regenerated.
+// input): each variant is tuned on its largest image among the candidates
+// that the batched kernel can hold, then the batched kernel is regenerated.
 fbcorr_status tune_batched(Plan* p, void* workspace, size_t workspace_bytes, hipStream_t s,
                            const fbcorr_tune_opts* opts, fbcorr_tune_report* report) {
     BatchedState* st = p->bstate;
@@ -399,7 +492,7 @@ fbcorr_status tune_batched(Plan* p, void* workspace, size_t workspace_bytes, hip
     fbcorr_tune_opts o{};
     if (opts) o = *opts;
     o.role = FBCORR_ROLE_FORWARD;
-    o.flags &= ~(1u | 4u);      // no direct variants in the persistent kernel
+    o.flags &= ~(1u | 4u);      // no direct variants in the batched kernel
     const bool record = opts && (opts->flags & 2u);
     fbcorr_tune_report total;
     memset(&total, 0, sizeof total);
@@ -423,7 +516,7 @@ fbcorr_status tune_batched(Plan* p, void* workspace, size_t workspace_bytes, hip
         total.best_ms += r.best_ms;
         total.default_ms += r.default_ms;
         const KeyT key = std::make_tuple(bv.fh, bv.fw, bv.D, bv.N);
-        if (four_waves(best)) {
+        if (batched_form(best)) {
             chosen[key] = best;
             if (record) {
                 std::string err;
@@ -433,7 +526,7 @@ fbcorr_status tune_batched(Plan* p, void* workspace, size_t workspace_bytes, hip
             }
         }
     }
-    // regenerate the persistent kernel with the chosen variants
+    // regenerate the batched kernel with the chosen variants
     std::unique_ptr<BatchedState> ns(new BatchedState());
     KernelSource ks;
     fbcorr_status e = prepare_batched(p->dev, (int32_t)st->descs.size(), st->descs.data(), ns.get(), ks, &chosen);
@@ -441,14 +534,14 @@ fbcorr_status tune_batched(Plan* p, void* workspace, size_t workspace_bytes, hip
     e = load_kernel(ks, p->device, ns->kernel);
     if (e != FBCORR_OK) return e;
     KernelSource rs = ks;
-    rs.name = "fbcorr_batched_reset";
-    e = load_kernel(rs, p->device, ns->reset);
+    rs.name = "fbcorr_batched_pack";
+    e = load_kernel(rs, p->device, ns->pack);
     if (e != FBCORR_OK) return e;
     int per_cu = 0;
     if (hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, ns->kernel.fn, 256, 0) != hipSuccess || per_cu < 1)
         per_cu = 1;
     ns->per_cu = per_cu;
-    ns->grid = (int)std::max<int64_t>(1, std::min<int64_t>(ns->nitems, (int64_t)p->dev.cus * per_cu));
+    ns->grid = (int)ns->nitems;
     destroy_batched(p);
     p->batch_ws = ns->ws_bytes;
     p->bstate = ns.release();
@@ -506,6 +599,9 @@ extern "C" fbcorr_status fbcorr_forward_batched(fbcorr_plan_t plan, const float*
             if (e == hipSuccess)
                 e = hipMemcpyAsync(base + st->off_imgs, st->imgs.data(), st->imgs.size() * 4,
                                    hipMemcpyHostToDevice, s);
+            if (e == hipSuccess && !st->cols.empty())
+                e = hipMemcpyAsync(base + st->off_cols, st->cols.data(), st->cols.size() * 4, hipMemcpyHostToDevice,
+                                   s);
             if (e == hipSuccess) e = hipStreamSynchronize(s);
             FBC_RETURN_IF(e != hipSuccess, FBCORR_ERR_LAUNCH, std::string("table upload: ") + hipGetErrorString(e));
             st->uploaded.insert(workspace);

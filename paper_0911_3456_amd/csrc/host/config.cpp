@@ -157,7 +157,9 @@ struct Tiling {
 };
 
 // nsp: bf16 parts per fp32 value (3), or 1 for 16-bit operands.
-static double price_tiling(const Tiling& c, const CorrProblem& p, int nsp, const TilePrices& pr) {
+// shared: tiles of the batched kernel, two workgroups of four
+// waves per CU whatever the variant.
+static double price_tiling(const Tiling& c, const CorrProblem& p, int nsp, const TilePrices& pr, bool shared) {
     const int npl = c.kc / 8, nkg = 64 / c.mf, w = c.wm * c.wn, nm = nsp == 3 ? 6 : 1;
     const bool planes = c.kc % 8 == 0 && !(npl & (npl - 1));
     const int regs =
@@ -175,9 +177,9 @@ static double price_tiling(const Tiling& c, const CorrProblem& p, int nsp, const
     long lds = nsp * (planes ? (long)npl * tr * cdiv(tc, c.s) * c.s * 16
                              : ((long)tr * cdiv(tc * c.kc, 4) + 1) / 2 * 16);
     if (c.ste) lds = std::max(lds, (long)w * c.mf * (c.nt * c.mf + 8) * 4);
-    if (lds > 160 * 1024) return 1e30;
+    if (lds > (shared ? kBatchedLds : 160 * 1024)) return 1e30;
     const int wps = std::min(8, 512 / ((regs + 7) / 8 * 8));
-    const int occ = std::min({(int)(160 * 1024 / std::max(lds, 1L)), wps * 4 / w, 8});
+    const int occ = shared ? 2 : std::min({(int)(160 * 1024 / std::max(lds, 1L)), wps * 4 / w, 8});
     if (occ < 1) return 1e30;
     // the busiest CU runs q workgroups, cc at a time; later rounds even out
     const double n = (double)cdiv(wo, two) * cdiv(ho, th) * cdiv(p.cout, cb) * p.batch;
@@ -199,7 +201,7 @@ static double price_tiling(const Tiling& c, const CorrProblem& p, int nsp, const
     return t + seq * (nch * pr.chunk + steps * pr.step + mfma * pr.chain);
 }
 
-static Config cheapest_rgemm(const CorrProblem& p, int nsp) {
+static Config cheapest_rgemm(const CorrProblem& p, int nsp, bool shared = false) {
     const TilePrices& pr = nsp == 3 ? kSplitPrices : kLowpPrices;
     const int cin = p.cin, cout = p.cout;
     const long ho = p.hi + 2 * p.padh - p.fh + 1, wo = p.wi + 2 * p.padw - p.fw + 1;
@@ -239,10 +241,10 @@ static Config cheapest_rgemm(const CorrProblem& p, int nsp) {
                         if (ncol % s || (ncol / s > need && ncol != mf)) continue;
                         for (c.wm = 1; c.wm * c.wn <= 8; c.wm *= 2) {
                             const int w = c.wm * c.wn;
-                            if (w < 2 || (w == 2 && cdiv(cin, kc) > 2)) continue;
+                            if (shared ? w != 4 : w < 2 || (w == 2 && cdiv(cin, kc) > 2)) continue;
                             for (c.mr = 1; c.mr <= 8; c.mr *= 2)
                                 for (c.mt = 1; c.mt <= (nsp == 3 ? 4 : 8); c.mt *= 2) {
-                                    const double t = price_tiling(c, p, nsp, pr);
+                                    const double t = price_tiling(c, p, nsp, pr, shared);
                                     if (t < best_t) { best_t = t; best = c; }
                                 }
                         }
@@ -427,6 +429,10 @@ static Config plain_config(const fbcorr_desc& d, int role, int cus) {
     }
 }
 
+bool three_parts_window(const fbcorr_desc& d) {
+    return d.fh * d.fw * d.D > (d.D == 1 ? 64 : 16);
+}
+
 static Config heuristic_config(const fbcorr_desc& d, int role, int cus) {
     const bool lowp = d.precision != FBCORR_FP32;
     const int ho = d.H - d.fh + 1, wo = d.W - d.fw + 1;
@@ -438,12 +444,11 @@ static Config heuristic_config(const fbcorr_desc& d, int role, int cus) {
     // memory traffic (1x1 windows of 16 channels: 13.6 and 15.9 us; a single
     // channel, 5x5: 20 and 28 us).  The other kernels here need a launch for
     // the filters anyway.
-    const int window = d.fh * d.fw * d.D;
     Config c;
     if (role == FBCORR_ROLE_FORWARD && lowp)
         c = cheapest_rgemm({d.batch, d.H, d.W, d.D, d.N, d.fh, d.fw, 0, 0}, 1);
     else if (role == FBCORR_ROLE_FORWARD && d.algo != FBCORR_ALGO_DIRECT && flops >= 2.0e8 &&
-             window > (d.D == 1 ? 64 : 16))
+             three_parts_window(d))
         c = cheapest_rgemm({d.batch, d.H, d.W, d.D, d.N, d.fh, d.fw, 0, 0}, 3);
     else if (role == FBCORR_ROLE_BACKWARD_X)
         c = cheapest_rgemm({d.batch, ho, wo, d.N, d.D, d.fh, d.fw, d.fh - 1, d.fw - 1}, 3);
@@ -454,6 +459,16 @@ static Config heuristic_config(const fbcorr_desc& d, int role, int cus) {
         if (!cs.empty()) c = cs[0];
     }
     return c.algo.empty() ? plain_config(d, role, cus) : c;
+}
+
+bool batched_form(const Config& c) {
+    if (c.algo == "rgemm") return c.get("sp") == 1 && c.get("wpe") == 2 && c.get("wm") * c.get("wn") == 4;
+    return c.algo == "igemm" && c.get("wm") * c.get("wn") * c.get("ks") == 4;
+}
+
+Config batched_parts(const fbcorr_desc& d) {
+    // many images share the launch: priced on a chip full of this one
+    return cheapest_rgemm({64, d.H, d.W, d.D, d.N, d.fh, d.fw, 0, 0}, 3, true);
 }
 
 // ---------------------------------------------------------- geometry

@@ -31,6 +31,9 @@ struct RoleBuild {
 // for the packed bank of any filter bank up to a few million weights.
 constexpr size_t kNoAllocScratchBytes = 16u << 20;
 
+// LDS of a variant of the batched kernel: two workgroups per CU.
+constexpr int kBatchedLds = 80 * 1024 - 256;
+
 // Default configuration of a role: the tuning database's entry for this
 // hardware and problem if there is one, else the hand-written heuristic
 // (shrunk until it fits the device).
@@ -50,6 +53,14 @@ Config default_igemm(int cin, int cout, bool lowp);
 Config default_rgemm(int cin, int cout, bool lowp);
 Config default_direct(const fbcorr_desc& d);
 Config default_dw(const fbcorr_desc& d, int cus);
+// The cheapest three-part tiling of four waves for the persistent batched
+// kernel (no algorithm if none fits).
+Config batched_parts(const fbcorr_desc& d);
+// Whether the batched kernel can hold the configuration: four waves, and
+// (rgemm) three-part operands at two waves per SIMD.
+bool batched_form(const Config& c);
+// Windows long enough for three bf16 parts to pay.
+bool three_parts_window(const fbcorr_desc& d);
 // The cheapest `count` three-part filter-gradient tilings, cheapest first.
 std::vector<Config> dws_tilings(const fbcorr_desc& d, int cus, int count);
 // The configuration a text such as "algo=rgemm mt=2" describes for a role:

@@ -76,7 +76,7 @@ void timing_end(Plan* p, int role, hipStream_t s, hipEvent_t a);
 // tune.cpp
 size_t tune_workspace(Plan* p);
 fbcorr_status tune_plan(Plan* p, const float* x, const float* w, float* y, void* workspace, size_t workspace_bytes,
-                        hipStream_t s, const fbcorr_tune_opts* opts, bool four_waves, bool install,
+                        hipStream_t s, const fbcorr_tune_opts* opts, bool shared, bool install,
                         fbcorr_tune_report* report, Config* chosen_out);
 // batched.cpp
 fbcorr_status tune_batched(Plan* p, void* workspace, size_t workspace_bytes, hipStream_t s,

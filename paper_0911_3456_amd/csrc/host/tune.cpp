@@ -378,11 +378,10 @@ using namespace fbc;
 namespace fbc {
 
 // The tuning loop for one plan and role.  x, w, y may be NULL: then the
-// timing runs on the integer gate data as well.  With four_waves only
-// implicit-GEMM variants of exactly four waves are tried (the block size of
-// the persistent batched kernel).  install: put the winner into the plan.
+// timing runs on the integer gate data as well.  With shared only the
+// variants that the batched kernel can hold are tried.  install: put the winner into the plan.
 fbcorr_status tune_plan(Plan* p, const float* x, const float* w, float* y, void* workspace,
-                        size_t workspace_bytes, hipStream_t s, const fbcorr_tune_opts* opts, bool four_waves,
+                        size_t workspace_bytes, hipStream_t s, const fbcorr_tune_opts* opts, bool shared,
                         bool install, fbcorr_tune_report* report, Config* chosen_out) {
     {
         const int role = opts ? opts->role : FBCORR_ROLE_FORWARD;
@@ -458,12 +457,12 @@ fbcorr_status tune_plan(Plan* p, const float* x, const float* w, float* y, void*
         std::vector<RoleBuild> builds;
         for (auto& c : cands) {
             if ((int)builds.size() >= maxc) break;
-            if (four_waves && (c.algo != "igemm" || c.get("wm") * c.get("wn") * c.get("ks") != 4)) continue;
+            if (shared && !batched_form(c)) continue;
             RoleBuild rb;
             rep.n_tried++;
             if (!build_role(d, role, c, p->dev, rb, err)) { rep.n_rejected_resources++; continue; }
             // batched variants share one kernel: keep two workgroups per CU
-            if (four_waves && rb.main_geom.lds > p->dev.lds_per_block / 2) { rep.n_rejected_resources++; continue; }
+            if (shared && rb.main_geom.lds > kBatchedLds) { rep.n_rejected_resources++; continue; }
             if (rb.ws_bytes > workspace_bytes - t.role_ws) { rep.n_rejected_resources++; continue; }
             builds.push_back(rb);
         }

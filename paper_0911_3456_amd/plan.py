@@ -23,7 +23,7 @@ def _ptr(t: torch.Tensor | None):
 def _check_tensor(t: torch.Tensor, shape, name: str) -> None:
     if not t.is_cuda or t.dtype != torch.float32 or not t.is_contiguous():
         raise ValueError("%s must be a contiguous float32 GPU tensor" % name)
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:                  # (a torch.Size is a tuple)
         raise ValueError("%s has shape %s, expected %s" % (name, tuple(t.shape), tuple(shape)))
     if t.data_ptr() % 16:
         raise ValueError("%s must be 16-byte aligned" % name)
@@ -40,27 +40,14 @@ class Plan:
         self.desc = nat.make_desc(batch, H, W, D, N, fh, fw, precision, algo,
                                   nat.FLAG_OVERLAP_BACKWARD if overlap_backward else 0)
         self.shape = (batch, H, W, D, N, fh, fw)
+        self.x_shape = (batch, H, W, D)
+        self.w_shape = (N, fh, fw, D)
+        self.y_shape = (batch, H - fh + 1, W - fw + 1, N)
         self.precision = precision
         h = ctypes.c_void_p()
         nat.check(self.lib.fbcorr_plan(ctypes.byref(self.desc), self.device.index, ctypes.byref(h)))
         self.handle = h
         self._ws = {}
-
-    # -- shapes
-    @property
-    def x_shape(self):
-        b, H, W, D, _, _, _ = self.shape
-        return (b, H, W, D)
-
-    @property
-    def w_shape(self):
-        _, _, _, D, N, fh, fw = self.shape
-        return (N, fh, fw, D)
-
-    @property
-    def y_shape(self):
-        b, H, W, _, N, fh, fw = self.shape
-        return (b, H - fh + 1, W - fw + 1, N)
 
     @property
     def flops(self) -> int:
@@ -90,9 +77,10 @@ class Plan:
     def forward(self, x: torch.Tensor, w: torch.Tensor, y: torch.Tensor | None = None) -> torch.Tensor:
         _check_tensor(x, self.x_shape, "x")
         _check_tensor(w, self.w_shape, "w")
-        if y is None:
+        if y is None:                     # (contiguous and aligned as allocated)
             y = torch.empty(self.y_shape, dtype=torch.float32, device=self.device)
-        _check_tensor(y, self.y_shape, "y")
+        else:
+            _check_tensor(y, self.y_shape, "y")
         ws = self.workspace(0)
         nat.check(self.lib.fbcorr_forward(self.handle, _ptr(x), _ptr(w), _ptr(y), _ptr(ws),
                                           ws.numel() if ws is not None else 0,

@@ -6,6 +6,7 @@ every arithmetic step runs in the library's HIP kernels.
 from __future__ import annotations
 
 import ctypes
+import threading
 
 import torch
 
@@ -13,7 +14,9 @@ from . import _native as nat
 
 
 def _stream_handle(device: torch.device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+    # (current_stream(device).cuda_stream without the Stream object, which
+    # every call would build twice)
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def _ptr(t: torch.Tensor | None):
@@ -27,6 +30,9 @@ def _check_tensor(t: torch.Tensor, shape, name: str) -> None:
         raise ValueError("%s has shape %s, expected %s" % (name, tuple(t.shape), tuple(shape)))
     if t.data_ptr() % 16:
         raise ValueError("%s must be 16-byte aligned" % name)
+
+
+_MAX_WS = 16        # scratch buffers a plan keeps (pass, thread, stream)
 
 
 class Plan:
@@ -48,6 +54,7 @@ class Plan:
         nat.check(self.lib.fbcorr_plan(ctypes.byref(self.desc), self.device.index, ctypes.byref(h)))
         self.handle = h
         self._ws = {}
+        self._ws_lock = threading.Lock()
 
     @property
     def flops(self) -> int:
@@ -62,16 +69,35 @@ class Plan:
         return n.value
 
     def workspace(self, pass_: int) -> torch.Tensor | None:
+        """Scratch of the calling thread on the current stream (None if the
+        pass needs none).  A plan is shared by streams and threads, and what
+        one call packs here must not be overwritten by another before its
+        products have read it: calls on two streams, or two threads that
+        enqueue on one stream, never share a buffer.  Inside a graph capture
+        the buffer comes from the graph's own pool and is not kept, so that
+        replays do not meet eager calls in it.  At most _MAX_WS buffers are
+        kept per plan; one that is dropped returns to its stream's pool of
+        torch's allocator, in stream order."""
         n = self.workspace_size(pass_)
         if n == 0:
             return None
-        t = self._ws.get(pass_)
+        if torch.cuda.is_current_stream_capturing():
+            return self._scratch(n)
+        key = (pass_, threading.get_ident(), _stream_handle(self.device))
+        t = self._ws.get(key)
         if t is None or t.numel() < n:
-            t = torch.empty(n + 256, dtype=torch.uint8, device=self.device)
-            off = (-t.data_ptr()) % 256
-            t = t[off:off + n]
-            self._ws[pass_] = t
+            t = self._scratch(n)
+            with self._ws_lock:
+                self._ws.pop(key, None)
+                while len(self._ws) >= _MAX_WS:
+                    del self._ws[next(iter(self._ws))]      # the oldest
+                self._ws[key] = t
         return t
+
+    def _scratch(self, n: int) -> torch.Tensor:
+        t = torch.empty(n + 256, dtype=torch.uint8, device=self.device)
+        off = (-t.data_ptr()) % 256
+        return t[off:off + n]
 
     # -- compute
     def forward(self, x: torch.Tensor, w: torch.Tensor, y: torch.Tensor | None = None) -> torch.Tensor:
@@ -128,8 +154,8 @@ class Plan:
                                        ws.numel() if ws is not None else 0,
                                        ctypes.c_void_p(_stream_handle(self.device)),
                                        ctypes.byref(opts), ctypes.byref(rep)))
-        self._ws.pop(0, None)
-        self._ws.pop(1, None)
+        with self._ws_lock:
+            self._ws.clear()
         return rep.as_dict()
 
     # -- configuration and timing

@@ -29,7 +29,9 @@
  *    caller, and must stay valid until the work queued on `stream` is done.
  *    The library never allocates device memory for them; scratch space is
  *    the caller's workspace of at least fbcorr_workspace_size() bytes
- *    (16-byte aligned; NULL is allowed when that size is 0).
+ *    (16-byte aligned; NULL is allowed when that size is 0).  Default fp32
+ *    forwards of some size pack their bank there (fbcorr_forward says what
+ *    they do without).
  *  - `stream` is a hipStream_t passed as void*; NULL means the null stream.
  *    Kernels are queued on it asynchronously.
  *  - Accumulation is always float32.  Results never depend on timing: there
@@ -173,7 +175,11 @@ FBCORR_API fbcorr_status fbcorr_workspace_size(fbcorr_plan_t plan, int pass, siz
 
 /* ---- compute ------------------------------------------------------------
  * fbcorr_forward: y = correlation(x, w) as defined at the top of this file.
- * x, w, y: device pointers in the layouts above. */
+ * x, w, y: device pointers in the layouts above.  A plan with the default
+ * FP32 configuration also takes a NULL or too small workspace: it then runs
+ * on fp32 instructions without scratch, at about 0.6 times the rate (the
+ * first such call compiles and loads that kernel).  Any other plan returns
+ * FBCORR_ERR_WORKSPACE. */
 FBCORR_API fbcorr_status fbcorr_forward(fbcorr_plan_t plan, const float* x, const float* w, float* y,
                              void* workspace, size_t workspace_bytes, void* stream);
 
@@ -183,12 +189,14 @@ FBCORR_API fbcorr_status fbcorr_forward(fbcorr_plan_t plan, const float* x, cons
  * forward role's scratch -- the packed filter bank of the 16-bit and
  * register-streamed matrix-core kernels, or the tap-major filter copy of the
  * direct kernel's scalar-weight variant -- taken from a static device array
- * of 16 MiB instead of a caller workspace; it calls no allocator.  Each GPU
- * the library runs on holds its own array until the process ends (its
- * address is looked up once per device, on the first call there).  Every
- * call on one GPU shares that GPU's array: calls whose work overlaps on one
- * GPU (other streams, other threads, other plans) race and must be
- * serialised by the caller.  The kernels write every scratch byte they
+ * of 16 MiB instead of a caller workspace; it calls no allocator.  (A plan
+ * with the default FP32 configuration runs the kernel that fbcorr_forward
+ * runs without a workspace: it uses no scratch, its calls may overlap, and
+ * its first call loads that kernel.)  Each GPU the library runs on holds its
+ * own array until the process ends (its address is looked up once per
+ * device, on the first call there).  Every call that uses it shares its
+ * GPU's array: calls whose work overlaps on one GPU (other streams, other
+ * threads, other plans) race and must be serialised by the caller.  The kernels write every scratch byte they
  * read, so nothing needs clearing between calls.  A plan whose forward role
  * needs more than 16 MiB of scratch (fbcorr_workspace_size pass 0) gets
  * FBCORR_ERR_WORKSPACE and nothing is launched.  x, w, y as for

@@ -1056,6 +1056,21 @@ Config default_config(const fbcorr_desc& d, int role, const DeviceInfo& di) {
     return database_config(d, role, di, c) ? c : heuristic_default(d, role, di);
 }
 
+bool scratchless_forward(const fbcorr_desc& d, const DeviceInfo& di, const Config& current, Config& out) {
+    const int role = FBCORR_ROLE_FORWARD;
+    std::string text, err;
+    if (d.precision != FBCORR_FP32 || current.algo != "rgemm" || !current.get("sp")) return false;
+    Config c;
+    // (a problem whose fp32 instructions are an rgemm entry packs its bank too)
+    if (database_config(d, role, di, c) || tuning_db_lookup(di.arch, role, d, text, "rgemm")) return false;
+    if (heuristic_default(d, role, di).str() != current.str()) return false;
+    if (!database_config(d, role, di, c, "igemm")) c = plain_default(d, role, di);
+    RoleBuild rb;
+    if (!build_role(d, role, c, di, rb, err) || rb.ws_bytes) return false;
+    out = c;
+    return true;
+}
+
 bool config_from_text(const fbcorr_desc& d, int role, const DeviceInfo& di, const std::string& text,
                       bool reset_named, Config& out, std::string& err) {
     // A text that names an algorithm starts from that algorithm's

@@ -40,6 +40,11 @@ constexpr int kBatchedLds = 80 * 1024 - 256;
 Config default_config(const fbcorr_desc& d, int role, const DeviceInfo& di);
 Config heuristic_default(const fbcorr_desc& d, int role, const DeviceInfo& di);
 
+// Whether `current`, the forward configuration of a plan, is the default that
+// three bf16 parts gave it; then the configuration that the pass has without
+// them, which needs no scratch.
+bool scratchless_forward(const fbcorr_desc& d, const DeviceInfo& di, const Config& current, Config& out);
+
 // tuning_db.cpp
 std::string tuning_db_path();
 bool tuning_db_lookup(const std::string& arch, int role, const fbcorr_desc& d, std::string& cfg,

@@ -30,6 +30,10 @@ struct Plan {
     std::atomic<bool> have[FBCORR_ROLE_COUNT] = {{false}, {false}, {false}};
     std::mutex compile_mu;
     std::mutex mu;
+    // forward kernel without scratch beside a default that needs it, compiled
+    // at its first use (spare_forward): 0 not looked for, 1 there, 2 none
+    RoleExec spare;
+    std::atomic<int> spare_state{0};
     // kernel timing
     bool timing = false;
     std::vector<std::pair<hipEvent_t, hipEvent_t>> pending[FBCORR_ROLE_COUNT];
@@ -60,6 +64,7 @@ private:
 fbcorr_status validate_desc(const fbcorr_desc* d);
 fbcorr_status compile_role(Plan* p, int role, const Config& c);
 fbcorr_status ensure_role(Plan* p, int role);
+fbcorr_status spare_forward(Plan* p, const RoleExec** out);
 fbcorr_status launch(const Kernel& k, const LaunchGeom& g, hipStream_t s, void** args);
 fbcorr_status check_ptr(const void* p, const char* what);
 fbcorr_status check_ws(void* ws, size_t have, size_t need);

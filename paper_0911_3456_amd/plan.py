@@ -116,7 +116,8 @@ class Plan:
     def forward_noalloc(self, x: torch.Tensor, w: torch.Tensor, y: torch.Tensor) -> torch.Tensor:
         """fbcorr_forward_noalloc: the forward pass with the library's static
         device scratch instead of a workspace (y must be given: nothing is
-        allocated)."""
+        allocated).  Calls that overlap on a GPU must be serialised, but for
+        plans with the default fp32 configuration, which use none."""
         _check_tensor(x, self.x_shape, "x")
         _check_tensor(w, self.w_shape, "w")
         _check_tensor(y, self.y_shape, "y")

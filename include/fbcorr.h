@@ -77,8 +77,11 @@ typedef enum fbcorr_status {
  * vector units, or as exact sums of three bf16 values each on the bf16
  * matrix units (six products per pair, fp32 accumulation; no further from
  * the fp64 result than fp32 instructions).  Values for which that would not
- * hold -- non-zero magnitudes outside [2^-100, 2^100), infinities, NaNs --
- * are computed with fp32 instructions, workgroup by workgroup.
+ * hold are computed with fp32 instructions, workgroup by workgroup:
+ * infinities, NaNs, input or gradient magnitudes that are tiny or huge
+ * (non-zero below 2^-100; from 2^39 up for the longest windows, 2^60 for 1000
+ * values), filters from 2^25 up, and filters from 2^10 up that also hold
+ * magnitudes below 2^-135 of their largest.
  * BF16 and FP16 round x and w to nearest-even after scaling each filter by a
  * power of two, s_n = 2^-floor(log2 max|w[n]|), and divide the accumulated
  * result by s_n again (exact).  FP16 inputs keep their full float32 range:

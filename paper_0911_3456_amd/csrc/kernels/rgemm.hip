@@ -57,14 +57,27 @@
 // the end: the sum is then rounded once per 16 products instead of once per
 // product, and the error against fp64 is a third of the fp32 instructions'
 // (rms 7e-9 against 2.4e-8 of sum |x||w|, contractions of 144 to 16384; all
-// terms positive: 1.5e-7 against 4.2e-7 at 784).  Filters are scaled by a
-// power of two per filter, as for 16-bit operands, so their parts never
-// leave the bf16 range.  Input values are not: a workgroup whose tile holds
-// a non-zero magnitude outside [2^-100, 2^100), an infinity or a NaN -- or
-// whose filters hold a non-finite value -- computes its outputs with plain
-// fp32 fused multiply-adds instead (slow_tile).  Measured, forward calls with
-// fp32 instructions before and with three parts now: 1024x1024x8 with 16 5x5
-// filters 73.2 and 44.6 us, 480x640x3 with 32 7x7 42.4 and 24.3 us.
+// terms positive: 1.5e-7 against 4.2e-7 at 784).
+//
+// Range of the parts.  A part is exact while the value's last bit is at least
+// 2^-126, and a product of parts must not be lost below 2^-126 where fp32
+// would hold it, so both operands are scaled up by powers of two (exact, and
+// undone in UNSCALE): input values by 2^XSH, a filter so that its largest
+// magnitude lies in [2^WSH, 2^(WSH+1)).  With 24 and 32:
+//   input values: every last bit is at least 2^(24-149).
+//   filters below 2^10: likewise, whatever the range inside a filter.
+//   products: what falls below 2^-126 was below 2^(-182+e) before the
+//   scaling, for a filter of magnitude 2^e: no more than fp32 loses below
+//   2^-149 as long as e <= 24.
+//   sums: K values below 2^XHI stay below 2^127, XHI = 70 - log2 K.
+// Filters outside (2^25 and more; 2^10 and more beside magnitudes below
+// 2^-135 of the largest; non-finite values) are marked by the pack with an
+// UNSCALE of 0.  A workgroup that meets one of those, or whose tile holds a
+// non-zero magnitude outside [2^-100, 2^XHI), an infinity or a NaN, computes
+// its outputs with plain fp32 fused multiply-adds instead (slow_tile).
+// Measured, forward calls with fp32 instructions before and with three parts
+// now: 1024x1024x8 with 16 5x5 filters 73.2 and 44.6 us, 480x640x3 with 32
+// 7x7 42.4 and 24.3 us.
 //
 // Column shift S (narrow outputs).  A workgroup's NCOLW = WN*NT*MF matrix
 // columns are S shifts x CB = NCOLW/S output channels: column (s, c)
@@ -77,8 +90,8 @@
 //   problem  BATCH FH FW CIN COUT HI WI HO WO PADH PADW
 //   DT       0 fp32 operands, 1 bf16, 2 fp16, 3 fp32 operands as three bf16
 //            parts (1-3: B pre-scaled and rounded by the pack; UNSCALE[c]
-//            multiplies each output, and for 3 is 0 for a filter that holds
-//            a non-finite value)
+//            multiplies each output, and for 3 is 0 for a filter that the
+//            parts cannot hold)
 //   XMOFF    fp16 only: UNSCALE[XMOFF .. XMOFF+255] hold partial maxima of |x|
 //            (fbcorr_absmax); when the input reaches 2^15 it is scaled by
 //            2^-k while staged (max |x| * 2^-k < 2^15, inside the fp16
@@ -148,6 +161,8 @@ typedef _Float16 rg_f16x8 __attribute__((ext_vector_type(8)));
 #if DT == 3
 #define NSP 3                     // bf16 parts of a value
 #define NACC 2                    // accumulators per tile: hh, the small products
+#define XSH 24                    // powers of two of the scales (range of the parts, above)
+#define WSH 32
 #else
 #define NSP 1
 #define NACC 1
@@ -203,8 +218,10 @@ __device__ __forceinline__ void rg_split(const float* v, rg_u32x4& ch, rg_u32x4&
 // part)*64 + lane for column tile j = pc / MF, step t = cell / NKG, lane =
 // MF*(cell % NKG) + pc%MF.  16-bit operands and parts: e_c = floor(log2
 // max|w[c]|), values scaled by 2^-e_c (exact) and rounded to nearest even,
-// unscale[pc] = 2^e_c (an all-zero filter gets e_c = 0; three-part mode: 0
-// for a filter that holds a non-finite value).  FB_FLIP: the
+// unscale[pc] = 2^e_c (an all-zero filter gets e_c = 0).  Parts: scaled by
+// 2^s, s = WSH - e_c but at most 126 - XSH (filters below 2^-70 have bits to
+// spare), unscale[pc] = 2^-(s+XSH), or 0 for a filter that the parts cannot
+// hold.  FB_FLIP: the
 // filters are those of the input-gradient correlation, read from the
 // forward bank w[CIN][FH][FW][COUT] flipped in (u, v) with the channel axes
 // exchanged.
@@ -310,12 +327,14 @@ static __device__ RG_PACK_ATTR void rg_pack(RG_GLOBAL const float* __restrict__ 
     float held[HELD ? PER : 1][PE];
     float m = 0.f;
     bool fin = true;                  // every value finite
+    float lo = 3.402823466e38f;       // smallest non-zero magnitude of this thread
     auto scan = [&](const float* vals) {
 #pragma unroll
         for (int q = 0; q < PE; ++q) {
             m = fmaxf(m, fabsf(vals[q]));
 #if DT == 3
             fin = fin && fabsf(vals[q]) <= 3.402823466e38f;      // false for infinities and NaNs
+            lo = vals[q] != 0.f ? fminf(lo, fabsf(vals[q])) : lo;
 #endif
         }
     };
@@ -345,13 +364,15 @@ static __device__ RG_PACK_ATTR void rg_pack(RG_GLOBAL const float* __restrict__ 
         (void)frexpf(m, &ex);     // m = f * 2^ex, f in [0.5, 1)
         ex -= 1;                  // floor(log2 m)
     }
-    sc = ldexpf(1.0f, -ex);
 #if DT == 3
-    // a filter below 2^-127 keeps the largest finite scale (its parts are
-    // then short of bits only below 2^-149 of full scale)
-    if (ex < -126) { ex = -126; sc = ldexpf(1.0f, 126); }
-    if (threadIdx.x == 0) unscale[pc] = fin ? ldexpf(1.0f, ex) : 0.f;
+    const int se = WSH - ex < 126 - XSH ? WSH - ex : 126 - XSH;
+    sc = ldexpf(1.0f, se);
+    bool exact = fin && ex <= 24;
+    // last bits below 2^-126 (the same branch in every thread)
+    if (exact && se < 23) exact = !__syncthreads_or(lo * sc < 0x1p-103f);
+    if (threadIdx.x == 0) unscale[pc] = exact ? ldexpf(1.0f, -(se + XSH)) : 0.f;
 #else
+    sc = ldexpf(1.0f, -ex);
     if (threadIdx.x == 0) unscale[pc] = real ? ldexpf(1.0f, ex) : 0.f;
 #endif
 #else
@@ -360,6 +381,7 @@ static __device__ RG_PACK_ATTR void rg_pack(RG_GLOBAL const float* __restrict__ 
     (void)fin;
     (void)red;
 #endif
+    (void)lo;
     if (HELD) {
 #pragma unroll
         for (int i = 0; i < (HELD ? PER : 1); ++i) store_item(threadIdx.x + i * 256, held[i], sc);
@@ -480,6 +502,17 @@ static_assert(LIN || CIN % PE == 0 || KC == PE, "partial cells need KC == PE");
 
 template <bool V> struct RgBool { static constexpr bool value = V; };
 
+#if DT == 3
+constexpr int rg_log2(long n) {            // rounded up
+    int b = 0;
+    while ((1L << b) < n) ++b;
+    return b;
+}
+#define XHI (127 - XSH - (WSH + 1) - rg_log2((long)FH * FW * CIN))
+#else
+#define XHI 100
+#endif
+
 #ifdef FB_BATCHED
 template <typename T> __device__ __forceinline__ RG_GLOBAL T* rg_uniform(RG_GLOBAL T* p) {
     const unsigned long long a = (unsigned long long)p;
@@ -522,11 +555,11 @@ struct RgRange {
         hi = hi > a ? hi : a;
         lo = lo < a - 1u ? lo : a - 1u;              // zero wraps to the largest value
     }
-    // some non-zero magnitude outside [2^-100, 2^100)
-    __device__ __forceinline__ bool outside() const { return hi >= 0x71800000u || lo < 0x0d800000u - 1u; }
+    // some non-zero magnitude outside [2^-100, 2^XHI)
+    __device__ __forceinline__ bool outside() const { return hi >= (127u + XHI) << 23 || lo < 0x0d800000u - 1u; }
 };
 
-// Two values (scaled by xs, exact) rounded to nearest even, packed.
+// Two values (fp16: scaled by xs, exact) rounded to nearest even, packed.
 __device__ __forceinline__ unsigned rg_pair(const float a, const float b, const float xs) {
 #if DT == 2
     const unsigned lo = __builtin_bit_cast(unsigned short, (_Float16)(a * xs));
@@ -548,9 +581,9 @@ __device__ __forceinline__ void rg_put(rg_unit* __restrict__ dst, const float* v
     rg_unit h, m, l;
 #pragma unroll
     for (int i = 0; i < ITEM / 2; ++i) {
-        const float a = v[2 * i], b = v[2 * i + 1];
-        range.see(a);
-        range.see(b);
+        range.see(v[2 * i]);
+        range.see(v[2 * i + 1]);
+        const float a = v[2 * i] * xs, b = v[2 * i + 1] * xs;
         h[i] = rg_pair(a, b, xs);
         const float ra = a - __builtin_bit_cast(float, h[i] << 16);
         const float rb = b - __builtin_bit_cast(float, h[i] & 0xffff0000u);
@@ -716,13 +749,15 @@ __device__ __forceinline__ void rgemm_tile(
 #if DT == 2
     const int kx = rg_input_scale_exp(UNSCALE);
     const float xs = ldexpf(1.f, -kx), ys = ldexpf(1.f, kx);
+#elif DT == 3
+    const float xs = (float)(1 << XSH), ys = 1.f;       // (undone in UNSCALE)
 #else
     const float xs = 1.f, ys = 1.f;
 #endif
     (void)ys; (void)Wr;
 #if DT == 3
-    // a column of this block with a non-finite filter, or (below) a staged
-    // value that the parts cannot hold
+    // a column of this block with a filter, or (below) a staged value, that
+    // the parts cannot hold
     bool odd = false;
     for (int i = tid; i < NCOLW; i += NTHREADS) odd = odd || UNSCALE[cblk * NCOLW + i] == 0.f;
 #endif

@@ -78,9 +78,9 @@ typedef enum fbcorr_status {
  * matrix units (six products per pair, fp32 accumulation; no further from
  * the fp64 result than fp32 instructions).  Values for which that would not
  * hold are computed with fp32 instructions, workgroup by workgroup:
- * infinities, NaNs, input or gradient magnitudes that are tiny or huge
- * (non-zero below 2^-100; from 2^39 up for the longest windows, 2^60 for 1000
- * values), filters from 2^25 up, and filters from 2^10 up that also hold
+ * infinities, NaNs, huge input or gradient magnitudes (from 2^39 up for the
+ * longest windows, 2^60 for 1000 values; the filter gradient's below 2^-100
+ * too), filters from 2^25 up, and filters from 2^10 up that also hold
  * magnitudes below 2^-135 of their largest.
  * BF16 and FP16 round x and w to nearest-even after scaling each filter by a
  * power of two, s_n = 2^-floor(log2 max|w[n]|), and divide the accumulated

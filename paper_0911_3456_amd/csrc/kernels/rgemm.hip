@@ -73,8 +73,9 @@
 // Filters outside (2^25 and more; 2^10 and more beside magnitudes below
 // 2^-135 of the largest; non-finite values) are marked by the pack with an
 // UNSCALE of 0.  A workgroup that meets one of those, or whose tile holds a
-// non-zero magnitude outside [2^-100, 2^XHI), an infinity or a NaN, computes
-// its outputs with plain fp32 fused multiply-adds instead (slow_tile).
+// magnitude from 2^XHI up, an infinity or a NaN, computes its outputs with
+// plain fp32 fused multiply-adds instead (slow_tile); small tails, down to
+// subnormal numbers, stay on the matrix units.
 // Measured, forward calls with fp32 instructions before and with three parts
 // now: 1024x1024x8 with 16 5x5 filters 73.2 and 44.6 us, 480x640x3 with 32
 // 7x7 42.4 and 24.3 us.
@@ -545,18 +546,16 @@ __device__ __forceinline__ int rg_input_scale_exp(const float* __restrict__ UNSC
 #endif
 }
 
-// Largest magnitude, and smallest non-zero one, of the values staged by a
-// thread, as bit patterns (in the order of the magnitudes; infinities and
-// NaNs above every finite value).
+// Largest magnitude of the values staged by a thread, as a bit pattern (in
+// the order of the magnitudes; infinities and NaNs above every finite value).
 struct RgRange {
-    unsigned hi = 0u, lo = 0xffffffffu;
+    unsigned hi = 0u;
     __device__ __forceinline__ void see(const float v) {
         const unsigned a = __builtin_bit_cast(unsigned, v) & 0x7fffffffu;
         hi = hi > a ? hi : a;
-        lo = lo < a - 1u ? lo : a - 1u;              // zero wraps to the largest value
     }
-    // some non-zero magnitude outside [2^-100, 2^XHI)
-    __device__ __forceinline__ bool outside() const { return hi >= (127u + XHI) << 23 || lo < 0x0d800000u - 1u; }
+    // some magnitude of 2^XHI or more
+    __device__ __forceinline__ bool outside() const { return hi >= (127u + XHI) << 23; }
 };
 
 // Two values (fp16: scaled by xs, exact) rounded to nearest even, packed.
@@ -657,35 +656,80 @@ constexpr int rg_lcm(int a, int b) {
 
 #if DT == 3
 // The tile's outputs by plain fp32 fused multiply-adds from the filters as
-// they are: for the rare tile whose values the bf16 parts cannot hold.
+// they are: for the rare tile whose values the bf16 parts cannot hold.  A
+// lane has one pixel and a wave SQ filters, the same in every lane: an input
+// value that is loaded serves SQ products, and pixels outside the image take
+// no part (their zeros would turn an infinite weight into a NaN).  With 8
+// filters, 96x110x16 and 64 7x7 filters with a huge value in every tile 82
+// us, fp32 instructions throughout 31 us, one filter at a time 1076 us.  The
+// batched kernel's bodies are functions: past 30 scalar registers they save
+// their return address, two scratch accesses per lane and tile (32 images of
+// ordinary values: 2 % slower with 8 filters).
+#ifdef FB_BATCHED
+#define SQ 2
+#define SKU 1
+#else
+#define SQ 8
+#define SKU 2
+#endif
 __device__ __forceinline__ void slow_tile(const float* __restrict__ Ib, const float* __restrict__ Wr,
                                           float* __restrict__ Ob, const int hi_, const int wi_, const int ho_,
                                           const int wo_, const int oi0, const int oj0, const int c0) {
     (void)hi_; (void)wi_; (void)ho_; (void)wo_;
+    constexpr int PGS = (TH * TWO + 63) / 64, QGS = (CB + SQ - 1) / SQ;
+    constexpr int KV = CIN % 4 == 0 ? 4 : 1;                  // input values per load
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll 1
-    for (int e = threadIdx.x; e < TH * TWO * CB; e += NTHREADS) {
-        const int oj = oj0 + e % TWO, oi = oi0 + e / TWO % TH, c = c0 + e / (TWO * TH);
-        if (oi >= HO || oj >= WO || c >= COUT) continue;
-        float val = 0.f;
+    for (int item = wave; item < PGS * QGS; item += NTHREADS / 64) {
+        const int e = item % PGS * 64 + lane, cq = c0 + item / PGS * SQ;
+        if (cq >= COUT) break;
+        const int oi = oi0 + e / TWO, oj = oj0 + e % TWO;
+        const bool real = e < TH * TWO && oi < HO && oj < WO;
+        float acc[SQ];
+#pragma unroll
+        for (int q = 0; q < SQ; ++q) acc[q] = 0.f;
 #pragma unroll 1
         for (int u = 0; u < FH; ++u)
 #pragma unroll 1
             for (int v = 0; v < FW; ++v) {
                 const int ii = oi + u - PADH, jj = oj + v - PADW;
-                if (ii < 0 || ii >= HI || jj < 0 || jj >= WI) continue;
-#pragma unroll 1
-                for (int k = 0; k < CIN; ++k)
+                if (real && ii >= 0 && ii < HI && jj >= 0 && jj < WI) {
+                    const float* const px = Ib + ((long)ii * WI + jj) * CIN;
+#pragma unroll SKU
+                    for (int k = 0; k < CIN; k += KV) {
+                        float xv[KV], wv[KV][SQ];
+#pragma unroll
+                        for (int i = 0; i < KV; ++i) xv[i] = px[k + i];
+#pragma unroll
+                        for (int q = 0; q < SQ; ++q) {
+                            const int c = cq + q < COUT ? cq + q : COUT - 1;
+#pragma unroll
+                            for (int i = 0; i < KV; ++i)
 #ifdef FB_FLIP
-                    val = fmaf(Ib[((long)ii * WI + jj) * CIN + k],
-                               Wr[(((long)k * FH + (FH - 1 - u)) * FW + (FW - 1 - v)) * COUT + c], val);
+                                wv[i][q] = Wr[(((long)(k + i) * FH + (FH - 1 - u)) * FW + (FW - 1 - v)) * COUT + c];
 #else
-                    val = fmaf(Ib[((long)ii * WI + jj) * CIN + k], Wr[(((long)c * FH + u) * FW + v) * CIN + k], val);
+                                wv[i][q] = Wr[(((long)c * FH + u) * FW + v) * CIN + k + i];
 #endif
+                        }
+#pragma unroll
+                        for (int i = 0; i < KV; ++i)
+#pragma unroll
+                            for (int q = 0; q < SQ; ++q) acc[q] = fmaf(xv[i], wv[i][q], acc[q]);
+                    }
+                }
             }
+        if (real)
+#pragma unroll
+            for (int q = 0; q < SQ; ++q)
+                if (cq + q < COUT && item / PGS * SQ + q < CB) {
+                    float val = acc[q];
+                    const int c = cq + q;
+                    (void)c;
 #ifdef FB_EPILOGUE
-        val = FB_EPILOGUE(val, c);
+                    val = FB_EPILOGUE(val, c);
 #endif
-        Ob[((long)oi * WO + oj) * COUT + c] = val;
+                    Ob[((long)oi * WO + oj) * COUT + c] = val;
+                }
     }
 }
 #endif

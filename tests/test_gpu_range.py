@@ -106,3 +106,95 @@ def test_batched(big, tiny, xs):
     assert "sp=1" in plan.describe()
     for x, w, y in zip(xs_, ws, plan.forward(list(to_dev(*xs_)), list(to_dev(*ws)))):
         _close(host(y)[None], *_corr(x[None], w))
+
+
+# ------------------------------------------------------------ small tails
+
+def _tails(rng, shape, density=0.004):
+    """Ordinary values with a few tiny ones, down to the subnormal range."""
+    a = rng.standard_normal(shape).astype(np.float32)
+    m = rng.random(shape) < density
+    a[m] *= (2.0 ** rng.uniform(-148, -100, size=int(m.sum()))).astype(np.float32)
+    return a
+
+
+def _times(fns, reps=10, rounds=5):
+    """Best time of each call, taken in turn."""
+    import torch
+    best = [1e9] * len(fns)
+    for f in fns:
+        f()
+    for _ in range(rounds):
+        for k, f in enumerate(fns):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(reps):
+                f()
+            b.record()
+            torch.cuda.synchronize()
+            best[k] = min(best[k], a.elapsed_time(b) / reps)
+    return best
+
+
+def test_tails_forward_and_input_gradient():
+    """The values' own accuracy, at the rate of ordinary values."""
+    need_gpu()
+    from paper_0911_3456_amd import Plan
+    rng = np.random.default_rng(8)
+    B, H, W, D, N, fh, fw = 4, 64, 66, 16, 64, 7, 7
+    p = Plan(B, H, W, D, N, fh, fw)
+    assert "sp=1" in p.get_config("forward") and "sp=1" in p.get_config("backward_x")
+    w = (rng.standard_normal((N, fh, fw, D)) * 0.03).astype(np.float32)
+    x, g = _tails(rng, (B, H, W, D)), _tails(rng, (B, H - fh + 1, W - fw + 1, N))
+    x[1], g[1] = x[1] * np.float32(1e-38), g[1] * np.float32(1e-38)      # an image of subnormal numbers
+    xt, wt, gt = to_dev(x, w, g)
+    _close(host(p.forward(xt, wt)), *_corr(x, w))
+    dx, _ = p.backward(xt, wt, gt, need_dw=False)
+    _close(host(dx), *_corr(np.pad(g, ((0, 0), (fh - 1, fh - 1), (fw - 1, fw - 1), (0, 0))),
+                            np.ascontiguousarray(w[:, ::-1, ::-1].transpose(3, 1, 2, 0))))
+    x0, g0 = to_dev(rng.standard_normal(x.shape).astype(np.float32), rng.standard_normal(g.shape).astype(np.float32))
+    a, b = _times([lambda: p.forward(xt, wt), lambda: p.forward(x0, wt)])
+    c, d = _times([lambda: p.backward(xt, wt, gt, need_dw=False), lambda: p.backward(x0, wt, g0, need_dw=False)])
+    print("forward %.4f and %.4f ms, input gradient %.4f and %.4f ms" % (a, b, c, d))
+    assert a < 1.5 * b and c < 1.5 * d
+
+
+def test_tails_batched():
+    need_gpu()
+    from paper_0911_3456_amd import BatchedPlan
+    rng = np.random.default_rng(9)
+    shapes = [(96, 120, 16, 64, 7, 7)] * 8
+    plan = BatchedPlan(shapes)
+    xs = [_tails(rng, s[:3]) for s in shapes]
+    ws = [rng.standard_normal((64, 7, 7, 16)).astype(np.float32) for _ in shapes]
+    xt, wt = list(to_dev(*xs)), list(to_dev(*ws))
+    _close(host(plan.forward(xt, wt)[3])[None], *_corr(xs[3][None], ws[3]))
+    x0 = list(to_dev(*[rng.standard_normal(s[:3]).astype(np.float32) for s in shapes]))
+    ys = plan.output_buffers()
+    a, b = _times([lambda: plan.forward(xt, wt, ys), lambda: plan.forward(x0, wt, ys)])
+    print("%.4f and %.4f ms" % (a, b))
+    assert a < 1.5 * b
+
+
+@pytest.mark.parametrize("shape", [(1, 96, 110, 16, 64, 7, 7), (1, 96, 150, 3, 64, 7, 7)])
+def test_huge_values_cost(shape):
+    """What the parts cannot hold (here a huge value in every tile) is right,
+    and within a small multiple of the time of fp32 instructions."""
+    need_gpu()
+    from paper_0911_3456_amd import Plan
+    rng = np.random.default_rng(10)
+    B, H, W, D, N, fh, fw = shape
+    p, q = Plan(*shape), Plan(*shape)
+    q.set_config("forward", "algo=igemm")
+    w = rng.standard_normal((N, fh, fw, D)).astype(np.float32)
+    x = rng.standard_normal((B, H, W, D)).astype(np.float32)
+    x[:, ::4, ::8, 0] = 3e38
+    xt, wt = to_dev(x, w)
+    y, y0 = host(p.forward(xt, wt)), host(q.forward(xt, wt))
+    ref, scl = _corr(x, w)
+    fin = (scl < 3e38)
+    _close(y[fin], ref[fin], scl[fin])
+    _close(y0[fin], ref[fin], scl[fin])
+    a, b = _times([lambda: p.forward(xt, wt), lambda: q.forward(xt, wt)])
+    print("%.4f ms, fp32 instructions %.4f ms" % (a, b))
+    assert a < 12 * b

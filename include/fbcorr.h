@@ -79,9 +79,10 @@ typedef enum fbcorr_status {
  * the fp64 result than fp32 instructions).  Values for which that would not
  * hold are computed with fp32 instructions, workgroup by workgroup:
  * infinities, NaNs, huge input or gradient magnitudes (from 2^39 up for the
- * longest windows, 2^60 for 1000 values; the filter gradient's below 2^-100
- * too), filters from 2^25 up, and filters from 2^10 up that also hold
- * magnitudes below 2^-135 of their largest.
+ * longest windows, 2^60 for 1000 values; in the filter gradient from 2^24 to
+ * 2^34 up, by the pixels that a workgroup sums), filters from 2^25 up, and
+ * filters from 2^10 up that also hold magnitudes below 2^-135 of their
+ * largest.
  * BF16 and FP16 round x and w to nearest-even after scaling each filter by a
  * power of two, s_n = 2^-floor(log2 max|w[n]|), and divide the accumulated
  * result by s_n again (exact).  FP16 inputs keep their full float32 range:

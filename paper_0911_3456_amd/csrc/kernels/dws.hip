@@ -37,9 +37,12 @@
 // g + NP, ... and writes its sums to part[g][n][q]; a separate kernel adds
 // the NP partials in a fixed order, so results do not depend on timing.
 //
-// A workgroup that staged a non-zero magnitude outside [2^-100, 2^63), an
-// infinity or a NaN computes its sums with plain fp32 fused multiply-adds
-// instead: its parts or its products might leave the bf16 or fp32 range.
+// Range of the parts: x and dy are scaled by 2^XSH while staged (undone at
+// the end, both exact), so that every last bit, of subnormal numbers too, is
+// at least 2^-126 and no product is lost that fp32 would hold.  Sums of the
+// PIXW pixels of a workgroup stay below 2^127 for magnitudes below 2^XHI.  A
+// workgroup that staged a larger one, an infinity or a NaN computes its sums
+// again with fp32 matrix instructions straight from memory.
 //
 // Measured against the kernel of fp32 instructions: 32 images 128x128x16, 64
 // 7x7 filters, 451 and 237 us; 24 problems of 1 to 100 channels 1.0 to 3.6
@@ -125,20 +128,31 @@ constexpr int max_rows() {
 #define XROWI (COPIES * XRE / 4)                  // groups of 4 x values per row
 #define XITEMS (RH * XROWI)
 #define XPER ((XITEMS + NTHREADS - 1) / NTHREADS)
+#define XSH 24
+// most pixels that one workgroup sums, and the magnitude's limit
+#define PIXW ((long)((NSEG + NP - 1) / NP) * RSEG * RW)
+#define XHI ((127 - 2 * XSH - log2_up(PIXW)) / 2)
 // the A fragments of the next 32 pixels are read ahead while they fit
 #define AHEAD (RT * CTM * 8 + RT * 24 + 24 <= 152)
 
 static_assert(RW % 16 == 0 && PXS % 32 == 0, "whole instructions per step");
 
+constexpr int log2_up(long n) {
+    int b = 0;
+    while ((1L << b) < n) ++b;
+    return b;
+}
+
+// Largest magnitude of the values staged by a thread, as a bit pattern
+// (infinities and NaNs above every finite value).
 struct DsRange {
-    unsigned hi = 0u, lo = 0xffffffffu;
+    unsigned hi = 0u;
     __device__ __forceinline__ void see(const float v) {
         const unsigned a = __builtin_bit_cast(unsigned, v) & 0x7fffffffu;
         hi = hi > a ? hi : a;
-        lo = lo < a - 1u ? lo : a - 1u;              // zero wraps to the largest value
     }
-    // some non-zero magnitude outside [2^-100, 2^63)
-    __device__ __forceinline__ bool outside() const { return hi >= 0x5f000000u || lo < 0x0d800000u - 1u; }
+    // some magnitude of 2^XHI or more
+    __device__ __forceinline__ bool outside() const { return hi >= (127u + XHI) << 23; }
 };
 
 __device__ __forceinline__ unsigned ds_pair(const float a, const float b) {
@@ -147,14 +161,14 @@ __device__ __forceinline__ unsigned ds_pair(const float a, const float b) {
     return lo | (hi << 16);
 }
 
-// Four values as their three parts, PB bytes apart.
+// Four values, scaled, as their three parts, PB bytes apart.
 __device__ __forceinline__ void ds_put(unsigned char* dst, const int pb, const float* v, DsRange& range) {
     ds_u32x2 h, m, l;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const float a = v[2 * i], b = v[2 * i + 1];
-        range.see(a);
-        range.see(b);
+        range.see(v[2 * i]);
+        range.see(v[2 * i + 1]);
+        const float a = v[2 * i] * (float)(1 << XSH), b = v[2 * i + 1] * (float)(1 << XSH);
         h[i] = ds_pair(a, b);
         const float ra = a - __builtin_bit_cast(float, h[i] << 16);
         const float rb = b - __builtin_bit_cast(float, h[i] & 0xffff0000u);
@@ -408,27 +422,49 @@ fbcorr_dw_split(const float* __restrict__ x, const float* __restrict__ dy, float
 
     // Partial sums: part[g][n][q] (zeros from workgroups without segments).
     float* const out = part + (long)blockIdx.x * N * QTOT;
+    float os = 1.0f / (float)(1L << 2 * XSH);
     if (__builtin_amdgcn_readfirstlane(__syncthreads_or(range.outside()))) {
-        const int tl = first_tile(cb * NW), th = first_tile((cb + 1) * NW);
-#pragma unroll 1
-        for (int e = tid; e < RB * (th - tl) * 16; e += NTHREADS) {
-            const int q = tl * 16 + e % ((th - tl) * 16), n = n0 + e / ((th - tl) * 16);
-            const int u = q / R4, r = q % R4;
-            if (n >= N || q >= QP || r >= FWD) continue;
-            float s = 0.f;
-#pragma unroll 1
-            for (int seg = blockIdx.x; seg < NSEG; seg += NP) {
-                const int sb = seg / (NSTR * NRS), sj = seg / NRS % NSTR * RW, si = seg % NRS * RSEG;
-#pragma unroll 1
-                for (int i = si; i < si + RSEG && i < HO; ++i)
-#pragma unroll 1
-                    for (int j = sj; j < sj + RW && j < WO; ++j)
-                        s = fmaf(dy[(((long)sb * HO + i) * WO + j) * N + n],
-                                 x[(((long)sb * H + i + u) * W + j) * D + r], s);
-            }
-            out[(long)n * QTOT + u * FWD + r] = s;
+        // Values that the parts cannot hold: 16x16x4 fp32 products, four
+        // pixels of an output row at a time, lane group g its pixel g, each
+        // operand loaded where it is used (2 images 60x70x8, 64 7x7 filters,
+        // two such values: 24 us, with one sum per thread 185; without any 12,
+        // the kernel of fp32 instructions 18).
+        os = 1.f;
+        int to[CTM];
+#pragma unroll
+        for (int ct = 0; ct < CTM; ++ct) {
+            const int q = (t0 + ct) * 16 + li, u = q / R4, r = q % R4;
+            to[ct] = ct < nct && q < QP && r < FWD ? u * (W * D) + r : -1;
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int k = 0; k < 2; ++k) acc[rt][ct][k] = (ds_f32x4){0.f, 0.f, 0.f, 0.f};
         }
-        return;
+#pragma unroll 1
+        for (int seg = blockIdx.x; seg < NSEG; seg += NP) {
+            const int sb = seg / (NSTR * NRS), sj = seg / NRS % NSTR * RW, si = seg % NRS * RSEG;
+            const int cols = WO - sj < RW ? WO - sj : RW;
+#pragma unroll 1
+            for (int i = si; i < si + RSEG && i < HO; ++i) {
+                const float* const gr = dy + (((long)sb * HO + i) * WO + sj) * N + n0 + li;
+                const float* const xr = x + (((long)sb * H + i) * W + sj) * D;
+#pragma unroll 2
+                for (int j = 0; j < cols; j += 4) {
+                    const int p = j + g;
+                    float a[RT], bv[CTM];
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt)
+                        a[rt] = p < cols && n0 + rt * 16 + li < N ? gr[(long)p * N + rt * 16] : 0.f;
+#pragma unroll
+                    for (int ct = 0; ct < CTM; ++ct) bv[ct] = p < cols && to[ct] >= 0 ? xr[p * D + to[ct]] : 0.f;
+#pragma unroll
+                    for (int ct = 0; ct < CTM; ++ct)
+#pragma unroll
+                        for (int rt = 0; rt < RT; ++rt)
+                            acc[rt][ct][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[rt], bv[ct], acc[rt][ct][0], 0, 0, 0);
+                }
+            }
+        }
     }
 #pragma unroll
     for (int ct = 0; ct < CTM; ++ct) {
@@ -439,7 +475,7 @@ fbcorr_dw_split(const float* __restrict__ x, const float* __restrict__ dy, float
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int n = n0 + rt * 16 + 4 * g + k;
-                if (n < N) out[(long)n * QTOT + u * FWD + r] = acc[rt][ct][0][k] + acc[rt][ct][1][k];
+                if (n < N) out[(long)n * QTOT + u * FWD + r] = (acc[rt][ct][0][k] + acc[rt][ct][1][k]) * os;
             }
     }
 }

@@ -198,3 +198,70 @@ def test_huge_values_cost(shape):
     a, b = _times([lambda: p.forward(xt, wt), lambda: q.forward(xt, wt)])
     print("%.4f ms, fp32 instructions %.4f ms" % (a, b))
     assert a < 12 * b
+
+
+def _dw_ref(x, g, fh, fw):
+    x, g = x.astype(np.float64), g.astype(np.float64)
+    B, ho, wo, N = g.shape
+    g2 = g.reshape(-1, N).T
+    ref, scl = (np.zeros((N, fh, fw, x.shape[3])) for _ in range(2))
+    for u in range(fh):
+        for v in range(fw):
+            a = x[:, u:u + ho, v:v + wo].reshape(-1, x.shape[3])
+            ref[:, u, v], scl[:, u, v] = g2 @ a, np.abs(g2) @ np.abs(a)
+    return ref, scl
+
+
+def _dw_close(got, x, g, fh, fw):
+    ref, scl = _dw_ref(x, g, fh, fw)
+    err = np.abs(got.astype(np.float64) - ref)
+    # (a sum of that many products, each as far off as fp32 has subnormal ones)
+    bad = err > TOL * scl + g.shape[0] * g.shape[1] * g.shape[2] * 2.0 ** -149
+    assert not bad.any(), (got[bad][:3], ref[bad][:3])
+
+
+DW = (2, 60, 70, 8, 64, 7, 7)
+
+
+def _dw_plan(shape=DW):
+    from paper_0911_3456_amd import Plan
+    p = Plan(*shape)
+    assert "dws" in p.get_config("backward_w")
+    return p
+
+
+@pytest.mark.parametrize("sx,sg", [(1.0, 1.0), (1e-25, 1e-14), (1e-18, 1e-18), (1e-30, 1e8), (1e-42, 1e8), (1e9, 1e-44),
+                                   (1e12, 1e12), (1e-39, 1e36)])
+def test_filter_gradient_scales(sx, sg):
+    """Whole tensors far from one: tiny times tiny, tiny times large."""
+    need_gpu()
+    rng = np.random.default_rng(11)
+    B, H, W, D, N, fh, fw = DW
+    x = (rng.standard_normal((B, H, W, D)) * sx).astype(np.float32)
+    g = (rng.standard_normal((B, H - fh + 1, W - fw + 1, N)) * sg).astype(np.float32)
+    w = np.zeros((N, fh, fw, D), np.float32)
+    _dw_close(host(_dw_plan().backward(*to_dev(x, w, g), need_dx=False)[1]), x, g, fh, fw)
+
+
+@pytest.mark.parametrize("shape", [DW, (1, 50, 61, 3, 33, 5, 4)])
+def test_tails_filter_gradient(shape):
+    need_gpu()
+    rng = np.random.default_rng(12)
+    B, H, W, D, N, fh, fw = shape
+    p = _dw_plan(shape)
+    x, g = _tails(rng, (B, H, W, D)), _tails(rng, (B, H - fh + 1, W - fw + 1, N))
+    g[..., 3] *= np.float32(1e-38)               # a filter of subnormal gradients
+    x[..., 1] *= np.float32(1e-38)
+    w = np.zeros((N, fh, fw, D), np.float32)
+    big = rng.standard_normal(x.shape).astype(np.float32)
+    big[0, 5, 7, 1], big[B - 1, H - 1, W - 1, 0] = 1e25, -1e22
+    xt, wt, gt, bt = to_dev(x, w, g, big)
+    _dw_close(host(p.backward(xt, wt, gt, need_dx=False)[1]), x, g, fh, fw)
+    _dw_close(host(p.backward(bt, wt, gt, need_dx=False)[1]), big, g, fh, fw)
+    x0, g0 = to_dev(rng.standard_normal(x.shape).astype(np.float32), rng.standard_normal(g.shape).astype(np.float32))
+    q = _dw_plan(shape)
+    q.set_config("backward_w", "algo=dw")
+    a, b, c, d = _times([lambda: p.backward(xt, wt, gt, need_dx=False), lambda: p.backward(x0, wt, g0, need_dx=False),
+                         lambda: p.backward(bt, wt, g0, need_dx=False), lambda: q.backward(bt, wt, g0, need_dx=False)])
+    print("tails %.4f, ordinary %.4f, huge %.4f ms, fp32 instructions %.4f" % (a, b, c, d))
+    assert a < 1.5 * b and c < 12 * d

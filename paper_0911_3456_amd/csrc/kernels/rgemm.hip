@@ -36,7 +36,8 @@
 // v_mfma_f32_{32x32x16,16x16x32} (8 values per lane); for fp32 it is four
 // v_mfma_f32_{32x32x2,16x16x4}_f32 (value q of the lane's cell in product
 // q).  A and B use the same order, so every padding value multiplies a zero
-// weight.
+// weight; it is zeroed itself first (mask_a), so that an infinity there does
+// not make a NaN.
 //
 // LDS layout of the input tile.  KC a power-of-two number of cells: planes
 // of 16-byte cells as above.  Any other KC (16-bit operands): the rows as
@@ -85,7 +86,10 @@
 // computes output column S*j + s of base pixel column j, with filter
 // B[(u, v', k), (s, c)] = Wt[c, u, v'-s, k] (zero outside 0 <= v'-s < FW)
 // over NTAPF = FW+S-1 taps per filter row; the pack writes each shifted
-// copy, and a lane's A run starts at pixel column S*j.
+// copy, and a lane's A run starts at pixel column S*j.  A run then holds
+// values that are outside some columns' windows: 16-bit tiles with infinities
+// or NaNs go to slow_tile (which costs ordinary tiles of narrow banks up to
+// 4 %: 65x424x16 with 9 7x7 filters 14.0 and 14.6 us).
 //
 // Compile-time constants (FB_<name>):
 //   problem  BATCH FH FW CIN COUT HI WI HO WO PADH PADW
@@ -172,6 +176,14 @@ typedef _Float16 rg_f16x8 __attribute__((ext_vector_type(8)));
 #define S FB_S
 #else
 #define S 1
+#endif
+// Tiles that hold what must not meet a zero weight are computed by slow_tile:
+// values outside the parts' range, and infinities and NaNs where a shifted
+// column's window is narrower than the run of taps that its lanes read.
+#if DT == 3 || (DT != 0 && S > 1)
+#define GUARD 1
+#else
+#define GUARD 0
 #endif
 #define NKG (64 / MF)             // lane groups of one instruction
 #define NPL (KC / PE)             // cell planes per channel chunk
@@ -511,7 +523,7 @@ constexpr int rg_log2(long n) {            // rounded up
 }
 #define XHI (127 - XSH - (WSH + 1) - rg_log2((long)FH * FW * CIN))
 #else
-#define XHI 100
+#define XHI 128                   // infinities and NaNs
 #endif
 
 #ifdef FB_BATCHED
@@ -591,10 +603,15 @@ __device__ __forceinline__ void rg_put(rg_unit* __restrict__ dst, const float* v
     }
     dst[0] = h; dst[SPU] = m; dst[2 * SPU] = l;
 #else
-    (void)range;
     rg_unit c;
 #pragma unroll
-    for (int i = 0; i < ITEM / 2; ++i) c[i] = rg_pair(v[2 * i], v[2 * i + 1], xs);
+    for (int i = 0; i < ITEM / 2; ++i) {
+        if (GUARD) {
+            range.see(v[2 * i]);
+            range.see(v[2 * i + 1]);
+        }
+        c[i] = rg_pair(v[2 * i], v[2 * i + 1], xs);
+    }
     dst[0] = c;
 #endif
 }
@@ -654,10 +671,10 @@ constexpr int rg_lcm(int a, int b) {
     return m;
 }
 
-#if DT == 3
+#if GUARD
 // The tile's outputs by plain fp32 fused multiply-adds from the filters as
-// they are: for the rare tile whose values the bf16 parts cannot hold.  A
-// lane has one pixel and a wave SQ filters, the same in every lane: an input
+// they are (16-bit operands: rounded as for the matrix units): for the rare
+// tile whose values the bf16 parts cannot hold (16-bit: not finite).  A lane has one pixel and a wave SQ filters, the same in every lane: an input
 // value that is loaded serves SQ products, and pixels outside the image take
 // no part (their zeros would turn an infinite weight into a NaN).  With 8
 // filters, 96x110x16 and 64 7x7 filters with a huge value in every tile 82
@@ -672,9 +689,23 @@ constexpr int rg_lcm(int a, int b) {
 #define SQ 8
 #define SKU 2
 #endif
+// A value as the products hold it: itself (three parts), or scaled by s and
+// rounded to nearest even.
+__device__ __forceinline__ float rg_rounded(const float v, const float s) {
+#if DT == 1
+    return (float)(__bf16)(v * s);
+#elif DT == 2
+    return (float)(_Float16)(v * s);
+#else
+    (void)s;
+    return v;
+#endif
+}
 __device__ __forceinline__ void slow_tile(const float* __restrict__ Ib, const float* __restrict__ Wr,
-                                          float* __restrict__ Ob, const int hi_, const int wi_, const int ho_,
-                                          const int wo_, const int oi0, const int oj0, const int c0) {
+                                          const float* __restrict__ us, float* __restrict__ Ob, const int hi_,
+                                          const int wi_, const int ho_, const int wo_, const int oi0, const int oj0,
+                                          const int c0, const float xs) {
+    (void)us; (void)xs;
     (void)hi_; (void)wi_; (void)ho_; (void)wo_;
     constexpr int PGS = (TH * TWO + 63) / 64, QGS = (CB + SQ - 1) / SQ;
     constexpr int KV = CIN % 4 == 0 ? 4 : 1;                  // input values per load
@@ -685,9 +716,12 @@ __device__ __forceinline__ void slow_tile(const float* __restrict__ Ib, const fl
         if (cq >= COUT) break;
         const int oi = oi0 + e / TWO, oj = oj0 + e % TWO;
         const bool real = e < TH * TWO && oi < HO && oj < WO;
-        float acc[SQ];
+        float acc[SQ], sc[SQ];
 #pragma unroll
-        for (int q = 0; q < SQ; ++q) acc[q] = 0.f;
+        for (int q = 0; q < SQ; ++q) {
+            acc[q] = 0.f;
+            sc[q] = DT == 3 ? 1.f : 1.f / us[cq + q < COUT ? cq - c0 + q : COUT - 1 - c0];
+        }
 #pragma unroll 1
         for (int u = 0; u < FH; ++u)
 #pragma unroll 1
@@ -699,7 +733,7 @@ __device__ __forceinline__ void slow_tile(const float* __restrict__ Ib, const fl
                     for (int k = 0; k < CIN; k += KV) {
                         float xv[KV], wv[KV][SQ];
 #pragma unroll
-                        for (int i = 0; i < KV; ++i) xv[i] = px[k + i];
+                        for (int i = 0; i < KV; ++i) xv[i] = rg_rounded(px[k + i], xs);
 #pragma unroll
                         for (int q = 0; q < SQ; ++q) {
                             const int c = cq + q < COUT ? cq + q : COUT - 1;
@@ -708,7 +742,7 @@ __device__ __forceinline__ void slow_tile(const float* __restrict__ Ib, const fl
 #ifdef FB_FLIP
                                 wv[i][q] = Wr[(((long)(k + i) * FH + (FH - 1 - u)) * FW + (FW - 1 - v)) * COUT + c];
 #else
-                                wv[i][q] = Wr[(((long)c * FH + u) * FW + v) * CIN + k + i];
+                                wv[i][q] = rg_rounded(Wr[(((long)c * FH + u) * FW + v) * CIN + k + i], sc[q]);
 #endif
                         }
 #pragma unroll
@@ -722,7 +756,7 @@ __device__ __forceinline__ void slow_tile(const float* __restrict__ Ib, const fl
 #pragma unroll
             for (int q = 0; q < SQ; ++q)
                 if (cq + q < COUT && item / PGS * SQ + q < CB) {
-                    float val = acc[q];
+                    float val = DT == 3 ? acc[q] : acc[q] / (sc[q] * xs);      // exact: powers of two
                     const int c = cq + q;
                     (void)c;
 #ifdef FB_EPILOGUE
@@ -799,10 +833,12 @@ __device__ __forceinline__ void rgemm_tile(
     const float xs = 1.f, ys = 1.f;
 #endif
     (void)ys; (void)Wr;
-#if DT == 3
-    // a column of this block with a filter, or (below) a staged value, that
-    // the parts cannot hold
+#if GUARD
+    // a staged value (below), or with parts a filter of this block, that
+    // slow_tile has to take
     bool odd = false;
+#endif
+#if DT == 3
     for (int i = tid; i < NCOLW; i += NTHREADS) odd = odd || UNSCALE[cblk * NCOLW + i] == 0.f;
 #endif
 
@@ -876,7 +912,7 @@ __device__ __forceinline__ void rgemm_tile(
                 if (e < SITEMS) rg_put(tile + dst, v[i], xs, range);
             }
         }
-#if DT == 3
+#if GUARD
         odd = odd || range.outside();
 #endif
         __syncthreads();
@@ -890,13 +926,34 @@ __device__ __forceinline__ void rgemm_tile(
 #pragma unroll
                 for (int p = 0; p < NSP; ++p) dst[mt][p] = rg_read(tile, o + mt * MR * RSU + p * SPU);
         };
+        // What meets zero weights -- the values past a row's taps, and (end:
+        // the chunk's last steps) the cells past the last -- is zeroed before
+        // its products: an infinity there would make them NaNs.
+        auto mask_a = [&](const int t, const int lim, rg_u32x4 (&src)[MT][NSP], auto end) {
+            constexpr int KEEP = PE - (CPR * PE - NTAPF * KC), PER = PE / 4;
+#pragma unroll
+            for (int k = 0; k < NKG; ++k) {
+                const int c = NKG * t + k;
+                const bool past = decltype(end)::value && c >= lim;
+                if (past || (KEEP < PE && c % CPR == CPR - 1)) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const unsigned m = past || i * PER >= KEEP ? 0u : (i + 1) * PER > KEEP ? 0xffffu : ~0u;
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt) src[mt][0][i] &= g == k ? m : ~0u;
+                    }
+                }
+            }
+        };
         read_a(0, 0, NCELL, a[0]);
 
-        // One step: read the next step's A fragments (step tn past unit
-        // offset base, lim cells left there), the products of this one, then refill this ring slot
+        // One step, t past unit offset base: read the next step's A fragments
+        // (step tn, lim cells left there), the products of this one, then refill this ring slot
         // with the fragments PF steps ahead (the packed bank has PF zero
         // steps after each chunk, so the refill needs no bounds test).
-        auto step = [&](const int base, const int tn, const int lim, const rg_u32x4* brow, const int r, const int ab) {
+        auto step = [&](const int base, const int t, const int tn, const int lim, const rg_u32x4* brow, const int r,
+                        const int ab, auto end) {
+            if (!GUARD) mask_a(t, lim, a[ab], end);
             read_a(base, tn, lim, a[ab ^ 1]);
 #if DT == 3
             // the small products first; neighbouring instructions on
@@ -947,7 +1004,7 @@ __device__ __forceinline__ void rgemm_tile(
             const rg_u32x4* bg = bc + (long)gi * G * NSP * 64;
             const int t0 = PERIODIC ? 0 : gi * G;
 #pragma unroll
-            for (int r2 = 0; r2 < G; ++r2) step(base, t0 + r2 + 1, NCELL, bg + r2 * NSP * 64, r2 % PF, r2 & 1);
+            for (int r2 = 0; r2 < G; ++r2) step(base, t0 + r2, t0 + r2 + 1, NCELL, bg + r2 * NSP * 64, r2 % PF, r2 & 1, RgBool<false>{});
             if (PERIODIC) base += G / PSTEPS * PROWS * RSU;
         }
         constexpr int REST = KSTEPS - NG * G;
@@ -955,14 +1012,17 @@ __device__ __forceinline__ void rgemm_tile(
         const int tr0 = PERIODIC ? 0 : NG * G, lim = PERIODIC ? NCELL - NG * G * NKG : NCELL;
 #pragma unroll
         for (int r2 = 0; r2 < REST; ++r2)
-            step(base, tr0 + (r2 + 1 < REST ? r2 + 1 : r2), lim, br + r2 * NSP * 64, r2 % PF, r2 & 1);
+            step(base, tr0 + r2, tr0 + (r2 + 1 < REST ? r2 + 1 : r2), lim, br + r2 * NSP * 64, r2 % PF, r2 & 1,
+                 RgBool<true>{});
     }
-#if DT == 3
+#if GUARD
     // (the same decision in every wave of the workgroup)
     if (__builtin_amdgcn_readfirstlane(__syncthreads_or(odd))) {
-        slow_tile(Ib, Wr, Ob, hi_, wi_, ho_, wo_, oi0, oj0, c0);
+        slow_tile(Ib, Wr, UNSCALE + cblk * NCOLW, Ob, hi_, wi_, ho_, wo_, oi0, oj0, c0, xs);
         return;
     }
+#endif
+#if DT == 3
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll

@@ -468,7 +468,8 @@ def precision_leg(steps: int, warmup: int, use_graph: bool = True):
 def batched_leg(steps: int, warmup: int):
     """256 uneven images (own bank each) in one launch replayed
     from a HIP graph: throughput over the whole batch; roofline from the
-    batched kernel's own duration (eager launches, events around it)."""
+    kernels' own duration, the packing of the banks included (eager launches,
+    events around them)."""
     import torch
     import workloads as wl
     from paper_0911_3456_amd import BatchedPlan
@@ -489,7 +490,7 @@ def batched_leg(steps: int, warmup: int):
             plan.launch(use_graph=False)
             plan.launch(use_graph=True)
         side.synchronize()
-        # the batched kernel alone (eager launches, events around it)
+        # the kernels alone (eager launches, events around them)
         plan.read_timing(reset=True)
         plan.enable_timing(True)
         for _ in range(reps):

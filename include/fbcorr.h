@@ -286,8 +286,8 @@ FBCORR_API fbcorr_status fbcorr_plan_set_epilogue(fbcorr_plan_t plan, const char
  * they are launched on, and accumulates the elapsed time when
  * fbcorr_plan_read_timing is called (which synchronises the events).
  * ms[role] = total milliseconds, calls[role] = role executions.  A batched
- * plan records role 0 around its batched kernel (eager launches) or its
- * graph launch. */
+ * plan records role 0 around its launches, the packing of its banks included
+ * (eager), or its graph launch. */
 FBCORR_API fbcorr_status fbcorr_plan_enable_timing(fbcorr_plan_t plan, int enable);
 FBCORR_API fbcorr_status fbcorr_plan_read_timing(fbcorr_plan_t plan, double* ms, int64_t* calls, int reset);
 

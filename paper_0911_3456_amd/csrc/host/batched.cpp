@@ -441,15 +441,14 @@ static fbcorr_status launch_batched(Plan* p, const float* const* xs, const float
     const void* imgs = base + st->off_imgs;
     const void* cols = base + st->off_cols;
     fbcorr_status r = FBCORR_OK;
+    hipEvent_t ev;
+    timing_begin(p, FBCORR_ROLE_FORWARD, s, ev);
     if (!st->cols.empty()) {
         void* a0[] = {(void*)&cols, (void*)&imgs, (void*)&wts, &base};
         r = launch(st->pack, LaunchGeom{(int)(st->cols.size() / 4), 1, 256, 0}, s, a0);
-        if (r != FBCORR_OK) return r;
     }
     void* a1[] = {(void*)&items, (void*)&imgs, (void*)&xs, (void*)&wts, (void*)&ys, &base};
-    hipEvent_t ev;
-    timing_begin(p, FBCORR_ROLE_FORWARD, s, ev);
-    r = launch(st->kernel, LaunchGeom{st->grid, 1, 256, 0}, s, a1);
+    if (r == FBCORR_OK) r = launch(st->kernel, LaunchGeom{st->grid, 1, 256, 0}, s, a1);
     timing_end(p, FBCORR_ROLE_FORWARD, s, ev);
     return r;
 }

@@ -273,9 +273,60 @@ static fbcorr_desc variant_key_desc(int fh, int fw, int D, int N) {
 }
 static const int kRoleBatched = 3;
 
+// Which keys gain from three-part products.  Packing reads and writes every
+// weight of every image (6 ps a weight, many banks), whatever the number of
+// output pixels; it pays where that is less than what the products save, 0.6
+// of the time on fp32 instructions (the rest is what three parts take).  That
+// time: a workgroup's staging and products one after another (63 ns per
+// contraction value; 95 where rows have fewer than 16 channels), 350
+// workgroups at a time, or the filters it reads (3 TB/s; 1.2 TB/s when all
+// banks together are past the last-level cache); for the whole batch at
+// least one workgroup's, shared by the keys as their parts are.  Measured,
+// us on fp32 instructions and with parts: 256 images of 64 channels with 256
+// 3x3 filters, 16 output pixels each 63 and 280, 256 pixels 219 and 397, 529
+// pixels 645 and 495; 48 of 32 channels with 512 9x9 filters, 16 pixels 289
+// and 454, 256 pixels 946 and 513; 32 of 32 with 128 11x11, 16 pixels 227
+// and 104.
+static std::set<KeyT> parts_that_pay(int32_t count, const fbcorr_desc* descs) {
+    struct Work { double weights = 0, wgs = 0, chain = 0, bytes = 0; };
+    std::map<KeyT, Work> keys;
+    double banks = 0;
+    for (int32_t i = 0; i < count; ++i) {
+        const fbcorr_desc& d = descs[i];
+        Config c = batched_variant_config(d.D, d.N);
+        const int s = c.get("s"), th = c.get("wm") * c.get("mt") * c.get("mr"), two = s * c.get("mf") / c.get("mr");
+        const int cb = c.get("wn") * c.get("nt") * c.get("mf") / s;
+        const double k = (double)d.fh * d.fw * d.D;
+        const double wgs = (double)cdiv(d.H - d.fh + 1, th) * cdiv(d.W - d.fw + 1, two) * cdiv(d.N, cb);
+        Work& w = keys[std::make_tuple(d.fh, d.fw, d.D, d.N)];
+        w.weights += k * d.N;
+        w.wgs += wgs;
+        w.chain = k * (d.D >= 16 ? 0.063 : 0.095);
+        w.bytes += wgs * std::min(cb, d.N) * k * 4;
+        banks += k * d.N * 4;
+    }
+    const double rate = banks > 192e6 ? 1.2e6 : 3e6;          // bytes per microsecond
+    auto plain = [&](const Work& w) { return std::max(w.chain * w.wgs / 350, w.bytes / rate); };
+    double sum = 0, chain = 0;
+    for (auto& kv : keys) {
+        sum += plain(kv.second);
+        chain = std::max(chain, kv.second.chain);
+    }
+    std::set<KeyT> out;
+    for (auto& kv : keys)
+        if (6e-6 * kv.second.weights < 0.6 * plain(kv.second) * std::max(1.0, chain / sum)) out.insert(kv.first);
+    return out;
+}
+
 static fbcorr_status prepare_batched(const DeviceInfo& dev, int32_t count, const fbcorr_desc* descs,
                                      BatchedState* st, KernelSource& ks,
                                      const std::map<KeyT, Config>* overrides = nullptr) {
+    for (int32_t i = 0; i < count; ++i) {
+        fbcorr_status s0 = validate_desc(&descs[i]);
+        if (s0 != FBCORR_OK) return s0;
+        FBC_RETURN_IF(descs[i].batch != 1, FBCORR_ERR_INVALID_ARGUMENT, "batched descriptors must have batch = 1");
+        FBC_RETURN_IF(descs[i].precision != FBCORR_FP32, FBCORR_ERR_UNSUPPORTED, "batched plans compute in fp32");
+    }
     std::map<KeyT, int> keyidx;
     std::map<KeyT, fbcorr_desc> largest;          // of each key, by input pixels
     for (int32_t i = 0; i < count; ++i) {
@@ -283,12 +334,9 @@ static fbcorr_status prepare_batched(const DeviceInfo& dev, int32_t count, const
         auto l = largest.emplace(std::make_tuple(d.fh, d.fw, d.D, d.N), d).first;
         if ((double)d.H * d.W > (double)l->second.H * l->second.W) l->second = d;
     }
+    const std::set<KeyT> pays = parts_that_pay(count, descs);
     for (int32_t i = 0; i < count; ++i) {
-        fbcorr_desc d = descs[i];
-        fbcorr_status s0 = validate_desc(&d);
-        if (s0 != FBCORR_OK) return s0;
-        FBC_RETURN_IF(d.batch != 1, FBCORR_ERR_INVALID_ARGUMENT, "batched descriptors must have batch = 1");
-        FBC_RETURN_IF(d.precision != FBCORR_FP32, FBCORR_ERR_UNSUPPORTED, "batched plans compute in fp32");
+        const fbcorr_desc d = descs[i];
         st->descs.push_back(d);
         auto key = std::make_tuple(d.fh, d.fw, d.D, d.N);
         auto it = keyidx.find(key);
@@ -317,8 +365,9 @@ static fbcorr_status prepare_batched(const DeviceInfo& dev, int32_t count, const
                 ok = true;
             }
             // three bf16 parts, but for windows too short to be anything but
-            // memory traffic (the single plans' line)
-            if (!ok && three_parts_window(d)) {
+            // memory traffic (the single plans' line), and banks that take
+            // longer to pack than their products save
+            if (!ok && three_parts_window(d) && pays.count(key)) {
                 const Config parts = batched_parts(largest[key]);
                 if (batched_form(parts) && fits(parts)) {
                     bv.cfg = parts;
@@ -359,7 +408,9 @@ static fbcorr_status prepare_batched(const DeviceInfo& dev, int32_t count, const
     // Work table, images with the costliest tiles first (stable).  Workgroups
     // go to the eight XCDs in turn: each XCD takes a contiguous part of an
     // image's tiles (shared halos stay in its L2), the longest part left once
-    // its own is used up.
+    // its own is used up.  An image of at most 16 tiles goes to one XCD as a
+    // whole, so that its bank is read into one L2 (128 images of two tiles
+    // with 128 11x11x32 filters: 325 us, 539 with the tiles side by side).
     for (int32_t i = 0; i < count; ++i) {
         const fbcorr_desc& d = st->descs[i];
         const BVariant& bv = st->vars[st->img_var[i]];
@@ -376,20 +427,33 @@ static fbcorr_status prepare_batched(const DeviceInfo& dev, int32_t count, const
         return (double)bv.th * bv.two * bv.cb * bv.fh * bv.fw * bv.D * (bv.parts() ? 1 : 2);
     };
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return tile_cost(a) > tile_cost(b); });
+    std::vector<std::pair<int32_t, int32_t>> queue[8];
+    double load[8] = {};
+    size_t total = 0;
     for (int32_t i : order) {
         const fbcorr_desc& d = st->descs[i];
         const BVariant& bv = st->vars[st->img_var[i]];
         const long nt = (long)cdiv(d.W - d.fw + 1, bv.two) * cdiv(d.H - d.fh + 1, bv.th) * cdiv(d.N, bv.cb);
-        FBC_RETURN_IF(st->items.size() / 4 + nt > 0x7fffffff, FBCORR_ERR_UNSUPPORTED, "too many tiles");
-        long at[8], end[8];
-        for (int x = 0; x < 8; ++x) { at[x] = nt * x / 8; end[x] = nt * (x + 1) / 8; }
+        total += nt;
+        FBC_RETURN_IF(total > 0x7fffffff, FBCORR_ERR_UNSUPPORTED, "too many tiles");
+        // few tiles: all on one XCD, the one with the least work
+        const int one = nt <= 16 ? (int)(std::min_element(load, load + 8) - load) : -1;
         for (long k = 0; k < nt; ++k) {
-            int x = (int)(st->items.size() / 4 % 8);
-            if (at[x] == end[x])
-                for (int z = 0; z < 8; ++z)
-                    if (end[z] - at[z] > end[x] - at[x]) x = z;
-            st->items.insert(st->items.end(), {st->img_var[i], i, (int32_t)at[x]++, 0});
+            const int x = one >= 0 ? one : (int)(k * 8 / nt);
+            queue[x].push_back({i, (int32_t)k});
+            load[x] += tile_cost(i);
         }
+    }
+    // workgroups go to the XCDs in turn
+    size_t at[8] = {}, left = 0;
+    for (auto& q : queue) left += q.size();
+    for (int x = 0; left > 0; --left, x = (x + 1) % 8) {
+        int z = x;
+        if (at[x] == queue[x].size())
+            for (int k = 0; k < 8; ++k)
+                if (queue[k].size() - at[k] > queue[z].size() - at[z]) z = k;
+        const auto& t = queue[z][at[z]++];
+        st->items.insert(st->items.end(), {st->img_var[t.first], t.first, t.second, 0});
     }
     st->nitems = (int64_t)(st->items.size() / 4);
     // workspace: items | image table | column table | packed banks and their

@@ -12,14 +12,14 @@ def test_timer_includes_the_packing():
     need_gpu()
     import torch
     from paper_0911_3456_amd import BatchedPlan
-    shapes = [(12, 12, 32, 512, 9, 9)] * 48          # 48 banks of 5 MB, 16 output pixels each
+    shapes = [(12, 12, 32, 512, 9, 9)] * 12          # 12 banks of 5 MB, 16 output pixels each
     plan = BatchedPlan(shapes)
     assert "sp=1" in plan.describe()
     xs = [torch.rand(s[:3], device="cuda") for s in shapes]
     ws = [torch.randn((s[3], s[4], s[5], s[2]), device="cuda") for s in shapes]
     plan.forward(xs, ws)
     torch.cuda.synchronize()
-    n = 20
+    n = 100
     plan.read_timing(reset=True)
     plan.enable_timing(True)
     a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)

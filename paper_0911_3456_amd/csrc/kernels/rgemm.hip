@@ -109,9 +109,9 @@
 //            XPADC (LDS row padding in cells), WPE (waves per SIMD the
 //            register budget is sized for), UNR (1: unroll the step loop
 //            completely), XCDMAP (XCD-aware workgroup order), NTS (1:
-//            non-temporal output stores), STE (1: tiles of whole column
-//            blocks store through LDS as 16-byte vectors, pixels past the
-//            image edge skipped)
+//            non-temporal output stores), STE (1: tiles store through LDS as
+//            16-byte vectors, pixels past the image edge and channels past
+//            COUT skipped)
 //   naming   KNAME   EPILOGUE(v, c) as in the LDS-staged kernel
 #ifndef __HIPCC_RTC__
 #include <hip/hip_runtime.h>
@@ -1036,6 +1036,7 @@ __device__ __forceinline__ void rgemm_tile(
     // and column l%16.  Workgroups whose tile lies inside the output store
     // without per-element bounds tests.
     const bool interior = oi0 + TH <= HO && oj0 + TWO <= WO && c0 + CB <= COUT;
+#if !STE
     auto store_all = [&](auto checked) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
@@ -1080,72 +1081,67 @@ __device__ __forceinline__ void rgemm_tile(
             }
         }
     };
-#if STE
-    if (c0 + CB <= COUT) {
-        // Stores through LDS: each pixel tile of the wave's columns goes to
-        // the wave's own LDS rows (the input tile is dead once every wave is
-        // past its last step) and back out as 16-byte vectors, so that one
-        // store instruction writes whole runs of a pixel's channels.  Every
-        // channel of the column block exists (COUT is a multiple of 4);
-        // pixels past the image edge are skipped per vector.
-        __syncthreads();
-        float* const sbuf = (float*)lds + wave * SWAVE;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const int col = (wn * NT + nt) * MF + lr;
-#if DT != 0
-                const float us = UNSCALE[cblk * NCOLW + col] * ys;      // exact: powers of two
-#endif
-#pragma unroll
-                for (int r = 0; r < NREG; ++r) {
-#if MF == 32
-                    const int m = 8 * (r >> 2) + 4 * g + (r & 3);
-#else
-                    const int m = 4 * g + r;
-#endif
-#if DT == 0
-                    float val = acc[mt][nt][0][r];
-#else
-                    float val = acc[mt][nt][0][r] * us;
-#endif
-#ifdef FB_EPILOGUE
-                    const int ch = c0 + col;      // (the macro's argument is used as it is)
-                    val = FB_EPILOGUE(val, ch);
-#endif
-                    sbuf[m * SROW + nt * MF + lr] = val;
-                }
-            }
-            // (the rows are exchanged between the lanes of the wave: every
-            // lane's writes come before any lane's reads, and those before
-            // the next tile's writes)
-            rg_wave_sync();
-            // MF rows of NT*MF/4 vectors, 64 per instruction
-#pragma unroll
-            for (int it = lane; it < MF * NT * MF / 4; it += 64) {
-                const int m = it / (NT * MF / 4), c4 = it % (NT * MF / 4);
-                const rg_f32x4 v = *(const rg_f32x4*)(sbuf + m * SROW + c4 * 4);
-                const int oi = oi0 + (wm * MT + mt) * MR + m / MC;
-                const int oj = oj0 + m % MC;
-                rg_f32x4* const dst =
-                    (rg_f32x4*)(Ob + (unsigned)((oi * WO + oj) * COUT + c0 + wn * NT * MF + c4 * 4));
-                if (interior || (oi < HO && oj < WO)) {
-#if defined(FB_NTS) && FB_NTS
-                    __builtin_nontemporal_store(v, dst);
-#else
-                    *dst = v;
-#endif
-                }
-            }
-            rg_wave_sync();
-        }
-    } else {
-        store_all(RgBool<true>{});
-    }
-#else
     if (interior) store_all(RgBool<false>{});
     else store_all(RgBool<true>{});
+#else
+    // Stores through LDS: each pixel tile of the wave's columns goes to
+    // the wave's own LDS rows (the input tile is dead once every wave is
+    // past its last step) and back out as 16-byte vectors, so that one
+    // store instruction writes whole runs of a pixel's channels.  A vector
+    // exists as a whole (COUT is a multiple of 4); those of pixels past
+    // the image edge and of channels past COUT are skipped.
+    __syncthreads();
+    float* const sbuf = (float*)lds + wave * SWAVE;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const int col = (wn * NT + nt) * MF + lr;
+#if DT != 0
+            const float us = UNSCALE[cblk * NCOLW + col] * ys;      // exact: powers of two
+#endif
+#pragma unroll
+            for (int r = 0; r < NREG; ++r) {
+#if MF == 32
+                const int m = 8 * (r >> 2) + 4 * g + (r & 3);
+#else
+                const int m = 4 * g + r;
+#endif
+#if DT == 0
+                float val = acc[mt][nt][0][r];
+#else
+                float val = acc[mt][nt][0][r] * us;
+#endif
+#ifdef FB_EPILOGUE
+                const int ch = c0 + col;      // (the macro's argument is used as it is)
+                val = FB_EPILOGUE(val, ch);
+#endif
+                sbuf[m * SROW + nt * MF + lr] = val;
+            }
+        }
+        // (the rows are exchanged between the lanes of the wave: every
+        // lane's writes come before any lane's reads, and those before
+        // the next tile's writes)
+        rg_wave_sync();
+        // MF rows of NT*MF/4 vectors, 64 per instruction
+#pragma unroll
+        for (int it = lane; it < MF * NT * MF / 4; it += 64) {
+            const int m = it / (NT * MF / 4), c4 = it % (NT * MF / 4);
+            const rg_f32x4 v = *(const rg_f32x4*)(sbuf + m * SROW + c4 * 4);
+            const int oi = oi0 + (wm * MT + mt) * MR + m / MC;
+            const int oj = oj0 + m % MC;
+            rg_f32x4* const dst =
+                (rg_f32x4*)(Ob + (unsigned)((oi * WO + oj) * COUT + c0 + wn * NT * MF + c4 * 4));
+            if (interior || (oi < HO && oj < WO && c0 + wn * NT * MF + c4 * 4 < COUT)) {
+#if defined(FB_NTS) && FB_NTS
+                __builtin_nontemporal_store(v, dst);
+#else
+                *dst = v;
+#endif
+            }
+        }
+        rg_wave_sync();
+    }
 #endif
 }
 

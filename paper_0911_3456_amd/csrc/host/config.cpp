@@ -435,6 +435,22 @@ bool three_parts_window(const fbcorr_desc& d) {
     return d.fh * d.fw * d.D > (d.D == 1 ? 64 : 16);
 }
 
+// Where the kernels that stage slices of the filters in LDS stay ahead: few
+// products per value staged or stored.  630 short-window problems, each kernel
+// timed: 4-byte stores (16 channels to 38, 1x1, in bf16: 31 us register-
+// streamed, 19 us), channel counts that are staged value by value (51 to 32,
+// 1x1: 29 and 20 us), windows without reuse of the staged tile (fp32, 51 to
+// 32, 1x1: 22 and 16 us), few channels to contract for many stored (input
+// gradient, 4 to 51, 3x1: 41 and 27 us).  Outside these lines the register-
+// streamed kernel is 1.4 to 1.75 times as fast on average there.
+static bool staged_slices_pay(int role, bool lowp, int cin, int cout, int fh, int fw) {
+    const int win = fh * fw;
+    const double per_value = 0.5 * win * cin * cout / (cin + cout);      // operations per byte
+    if (role == FBCORR_ROLE_BACKWARD_X) return cout > 16 && (win == 1 || (cin <= 8 && win <= 5));
+    if (!lowp) return win == 1 || win * cin < 36;
+    return (cout % 4 && per_value < 12) || (win == 1 && cin % 4 && cin > 16);
+}
+
 static Config heuristic_config(const fbcorr_desc& d, int role, int cus) {
     const bool lowp = d.precision != FBCORR_FP32;
     const int ho = d.H - d.fh + 1, wo = d.W - d.fw + 1;
@@ -443,10 +459,12 @@ static Config heuristic_config(const fbcorr_desc& d, int role, int cus) {
     // that repacks the filters from about 0.2 GFLOP on (fp32 instructions,
     // one launch, against this: 8.5 and 11.4 us at 0.1 GFLOP, 23 and 14 us
     // at 1.3), and not where the windows are too short to be anything but
-    // memory traffic (1x1 windows of 16 channels: 13.6 and 15.9 us; a single
-    // channel, 5x5: 20 and 28 us).  The other kernels here need a launch for
-    // the filters anyway.
+    // memory traffic (a single channel, 5x5: 20 and 28 us).  The other
+    // kernels here need a launch for the filters anyway.
     Config c;
+    const bool dx = role == FBCORR_ROLE_BACKWARD_X;
+    if (role != FBCORR_ROLE_BACKWARD_W && staged_slices_pay(role, lowp, dx ? d.N : d.D, dx ? d.D : d.N, d.fh, d.fw))
+        return plain_config(d, role, cus);
     if (role == FBCORR_ROLE_FORWARD && lowp)
         c = cheapest_rgemm({d.batch, d.H, d.W, d.D, d.N, d.fh, d.fw, 0, 0}, 1);
     else if (role == FBCORR_ROLE_FORWARD && d.algo != FBCORR_ALGO_DIRECT && flops >= 2.0e8 &&

@@ -265,7 +265,9 @@ FBCORR_API fbcorr_status fbcorr_plan_get_config(fbcorr_plan_t plan, int role, ch
 
 /* Replace the configuration of `role` by one given in the same text form
  * (keys not given keep their defaults: the tuning database's for this
- * problem, else the named algorithm's hand-written ones).  Compiles it; on
+ * problem, else the named algorithm's own; a text that names no algorithm
+ * and meets no entry describes igemm, or dw for the filter gradient, whatever
+ * runs now).  Compiles it; on
  * any error the previous configuration stays in place. */
 FBCORR_API fbcorr_status fbcorr_plan_set_config(fbcorr_plan_t plan, int role, const char* cfg);
 

@@ -1095,19 +1095,22 @@ bool config_from_text(const fbcorr_desc& d, int role, const DeviceInfo& di, cons
                       bool reset_named, Config& out, std::string& err) {
     // A text that names an algorithm starts from that algorithm's
     // hand-written defaults ("algo=direct" alone is a complete
-    // configuration), one that names none from those of the kernels that
-    // fit any size; where the database has an entry, unnamed knobs are the
-    // entry's instead (but not on the forward role with reset_named, if the
-    // text names an algorithm).
+    // configuration), "algo=dws" from the tilings' cheapest, one that names
+    // none from those of the kernels that fit any size; where the database
+    // has an entry (for a text without an algorithm: also one of a form that
+    // is not the problem's default), unnamed knobs are the entry's instead
+    // (but not on the forward role with reset_named, if the text names an
+    // algorithm).
     Config named;
     std::istringstream is(text);
     std::string tok;
     while (is >> tok)
         if (tok.compare(0, 5, "algo=") == 0) named.algo = tok.substr(5);
     Config c;
-    if (!database_config(d, role, di, c) &&
-        (named.algo.empty() || !database_config(d, role, di, c, named.algo)))
-        c = plain_default(d, role, di);
+    bool entry = database_config(d, role, di, c);
+    for (const char* form : {"igemm", "rgemm", "dw"})
+        if (!entry && (named.algo.empty() || named.algo == form)) entry = database_config(d, role, di, c, form);
+    if (!entry) c = plain_default(d, role, di);
     const int cin = role == FBCORR_ROLE_BACKWARD_X ? d.N : d.D;
     const int cout = role == FBCORR_ROLE_BACKWARD_X ? d.D : d.N;
     const bool lp = d.precision != FBCORR_FP32 && role == FBCORR_ROLE_FORWARD;
@@ -1116,6 +1119,10 @@ bool config_from_text(const fbcorr_desc& d, int role, const DeviceInfo& di, cons
     else if (named.algo == "igemm" && role != FBCORR_ROLE_BACKWARD_W && reset) c = default_igemm(cin, cout, lp);
     else if (named.algo == "rgemm" && role != FBCORR_ROLE_BACKWARD_W && reset) c = default_rgemm(cin, cout, lp);
     else if (named.algo == "dw" && role == FBCORR_ROLE_BACKWARD_W && other) c = plain_default(d, role, di);
+    else if (named.algo == "dws" && role == FBCORR_ROLE_BACKWARD_W && other) {
+        const std::vector<Config> cs = dws_tilings(d, di.cus, 1);
+        if (!cs.empty()) c = cs[0];
+    }
     if (!parse_config(text, c, err)) return false;
     out = c;
     return true;

@@ -178,10 +178,10 @@ static bool generate(BatchedState& st, KernelSource& ks, std::string& err) {
 extern "C" __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 fbcorr_batched(const int4* __restrict__ items, const int4* __restrict__ imgs,
                const float* const* __restrict__ xs, const float* const* __restrict__ wts,
-               float* const* __restrict__ ys, const char* __restrict__ ws)
+               float* const* __restrict__ ys, const char* __restrict__ ws, const int first)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds_raw[MAXLDS];
-    const int4 w = items[blockIdx.x];
+    const int4 w = items[first + blockIdx.x];
     const int4 im = imgs[2 * w.y], at = imgs[2 * w.y + 1];
     const float* x = xs[w.y];
     const float* wt = wts[w.y];
@@ -511,8 +511,12 @@ static fbcorr_status launch_batched(Plan* p, const float* const* xs, const float
         void* a0[] = {(void*)&cols, (void*)&imgs, (void*)&wts, &base};
         r = launch(st->pack, LaunchGeom{(int)(st->cols.size() / 4), 1, 256, 0}, s, a0);
     }
-    void* a1[] = {(void*)&items, (void*)&imgs, (void*)&xs, (void*)&wts, (void*)&ys, &base};
-    if (r == FBCORR_OK) r = launch(st->kernel, LaunchGeom{st->grid, 1, 256, 0}, s, a1);
+    int first = 0;
+    void* a1[] = {(void*)&items, (void*)&imgs, (void*)&xs, (void*)&wts, (void*)&ys, &base, &first};
+    // (a launch has less than 2^32 threads)
+    constexpr int kMostGroups = 0xffffffffu / 256;
+    for (; r == FBCORR_OK && first < st->grid; first += std::min(kMostGroups, st->grid - first))
+        r = launch(st->kernel, LaunchGeom{std::min(kMostGroups, st->grid - first), 1, 256, 0}, s, a1);
     timing_end(p, FBCORR_ROLE_FORWARD, s, ev);
     return r;
 }

@@ -123,7 +123,13 @@ static bool template_body(const std::string& file, Body& out, std::string& err) 
     const auto b0 = tpl.find("//@@BODY-BEGIN"), b1 = tpl.find("//@@BODY-END");
     if (b0 == std::string::npos || b1 == std::string::npos) { err = file + " template lacks body markers"; return false; }
     out.header = tpl.substr(0, b0);
-    out.text = tpl.substr(b0, b1 - b0);
+    // without comments: the text is repeated per key, and every plan hashes it
+    bool comment = false;
+    for (size_t i = b0; i < b1; ++i) {
+        if (tpl[i] == '\n') comment = false;
+        else if (tpl[i] == '/' && tpl[i + 1] == '/') comment = true;
+        if (!comment) out.text += tpl[i];
+    }
     out.macros = body_macros(out.text);
     return true;
 }

@@ -371,9 +371,12 @@ static fbcorr_status prepare_batched(const DeviceInfo& dev, int32_t count, const
                 ok = true;
             }
             // three bf16 parts, but for windows too short to be anything but
-            // memory traffic (the single plans' line), and banks that take
-            // longer to pack than their products save
-            if (!ok && three_parts_window(d) && pays.count(key)) {
+            // memory traffic, 1x1 windows of many channels, staged chunk by
+            // chunk for one use (16 images of 64 channels with 200 filters
+            // 355 us on fp32 instructions, 525 with parts; 32 of 33 with 60,
+            // 156 and 196), and banks that take longer to pack than their
+            // products save
+            if (!ok && three_parts_window(d) && (d.fh * d.fw > 1 || d.D <= 32) && pays.count(key)) {
                 const Config parts = batched_parts(largest[key]);
                 if (batched_form(parts) && fits(parts)) {
                     bv.cfg = parts;

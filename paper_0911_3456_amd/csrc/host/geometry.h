@@ -58,8 +58,8 @@ Config default_igemm(int cin, int cout, bool lowp);
 Config default_rgemm(int cin, int cout, bool lowp);
 Config default_direct(const fbcorr_desc& d);
 Config default_dw(const fbcorr_desc& d, int cus);
-// The cheapest three-part tiling of four waves for the persistent batched
-// kernel (no algorithm if none fits).
+// The cheapest three-part tiling of four waves for the batched kernel (no
+// algorithm if none fits).
 Config batched_parts(const fbcorr_desc& d);
 // Whether the batched kernel can hold the configuration: four waves, and
 // (rgemm) three-part operands at two waves per SIMD.

@@ -55,3 +55,10 @@ def test_workload_keeps_its_parts():
     shapes, _ = wl.draw_batched_list()
     plan = BatchedPlan([(s.H, s.W, s.D, s.N, s.fh, s.fw) for s in shapes])
     assert "algo=igemm" not in plan.describe()
+
+
+def test_single_pixel_windows():
+    need_gpu()
+    from paper_0911_3456_amd import BatchedPlan
+    for D, parts in ((32, True), (64, False), (33, False)):
+        assert ("sp=1" in BatchedPlan([(150, 150, D, 60, 1, 1)] * 32).describe()) == parts

@@ -1120,6 +1120,7 @@ bool config_from_text(const fbcorr_desc& d, int role, const DeviceInfo& di, cons
     else if (named.algo == "rgemm" && role != FBCORR_ROLE_BACKWARD_W && reset) c = default_rgemm(cin, cout, lp);
     else if (named.algo == "dw" && role == FBCORR_ROLE_BACKWARD_W && other) c = plain_default(d, role, di);
     else if (named.algo == "dws" && role == FBCORR_ROLE_BACKWARD_W && other) {
+        // (where none fits, the text has to name every knob)
         const std::vector<Config> cs = dws_tilings(d, di.cus, 1);
         if (!cs.empty()) c = cs[0];
     }

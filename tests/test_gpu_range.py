@@ -265,3 +265,40 @@ def test_tails_filter_gradient(shape):
                          lambda: p.backward(bt, wt, g0, need_dx=False), lambda: q.backward(bt, wt, g0, need_dx=False)])
     print("tails %.4f, ordinary %.4f, huge %.4f ms, fp32 instructions %.4f" % (a, b, c, d))
     assert a < 1.5 * b and c < 12 * d
+
+
+# ------------------------------------------------------------ the limits
+
+@pytest.mark.parametrize("side", [0.999, 1.0, 1.5])
+def test_limit_of_the_parts(side):
+    """Sums of equal signs right below, at and above the largest magnitude
+    that the matrix units take, with the largest filters that they take."""
+    need_gpu()
+    from paper_0911_3456_amd import Plan
+    B, H, W, D, N, fh, fw = 1, 40, 50, 16, 40, 5, 3
+    xhi = 70 - int(np.ceil(np.log2(fh * fw * D)))
+    rng = np.random.default_rng(13)
+    x = (rng.uniform(0.99, 1.0, (B, H, W, D)) * side * 2.0 ** xhi).astype(np.float32)
+    p = Plan(B, H, W, D, N, fh, fw)
+    p.set_config("forward", "algo=rgemm sp=1 mf=32 kc=8 mr=2 mt=1 nt=1 wm=2 wn=1 pf=2")
+    for wmax in (2.0 ** 25 * 0.9999, 2.0 ** 25, 2.0 ** -126, 2.0 ** -149):
+        w = np.full((N, fh, fw, D), wmax, np.float32)
+        _close(host(p.forward(*to_dev(x, w))), *_corr(x, w))
+
+
+@pytest.mark.parametrize("side", [0.999, 1.0, 1.5])
+def test_limit_of_the_filter_gradient(side):
+    need_gpu()
+    import re
+    from paper_0911_3456_amd import codegen, make_desc
+    B, H, W, D, N, fh, fw = DW
+    o = {k: int(v) for k, v in re.findall(r"-DFB_(\w+)=(\d+)", codegen(make_desc(*DW), "backward_w", None)[1])}
+    ho, wo = H - fh + 1, W - fw + 1
+    nseg = B * -(-wo // o["RW"]) * -(-ho // o["RSEG"])
+    pixels = -(-nseg // o["NP"]) * o["RSEG"] * o["RW"]
+    xhi = (127 - 48 - int(np.ceil(np.log2(pixels)))) // 2
+    rng = np.random.default_rng(14)
+    x = (rng.uniform(0.99, 1.0, (B, H, W, D)) * side * 2.0 ** xhi).astype(np.float32)
+    g = (rng.uniform(0.99, 1.0, (B, ho, wo, N)) * side * 2.0 ** xhi).astype(np.float32)
+    w = np.zeros((N, fh, fw, D), np.float32)
+    _dw_close(host(_dw_plan().backward(*to_dev(x, w, g), need_dx=False)[1]), x, g, fh, fw)

@@ -15,8 +15,10 @@ Also printed in the same JSON line:
                 launches, so dW includes the fixed-order sum of its partials):
                 algorithmic flops per execution over its average duration
                 from HIP events on the launch stream (eager pass, after the
-                warm-ups), against the MI355X fp32 matrix peak; traffic from
-                the committed rocprofv3 counter summary when it was taken on
+                warm-ups), against the MI355X bf16 matrix peak over six (six
+                bf16 products make an fp32 one; the fp32 matrix peak for
+                configurations of fp32 instructions); traffic from the
+                committed rocprofv3 counter summary when it was taken on
                 exactly these kernels.
   cpu_baseline  the FP64 oracle timed on this host: all cores on the whole
                 step, and one thread on one image of the batch.
@@ -33,8 +35,8 @@ Also printed in the same JSON line:
                 normalised error against FP64 oracle values stored at 132
                 sites x 128 filters (tests/golden/precision_sites.npz, written
                 by a script that runs only the oracle).
-  batched       256 uneven images with their own banks in one persistent
-                launch, replayed from a HIP graph, with its roofline.
+  batched       256 uneven images with their own banks in one launch,
+                replayed from a HIP graph, with its roofline.
   nearest_neighbour  exact brute-force nearest-neighbour search of 4096
                 8x8-pixel target patches against 4096 ... 1,048,576
                 neighbours (the sizes of the paper's search-time table,
@@ -62,6 +64,8 @@ FP32_MATRIX_PEAK_TFLOPS = 157.3     # dense fp32 matrix cores
 FP32_VECTOR_PEAK_TFLOPS = 157.3     # fp32 vector ALU: 256 CUs x 256 flop/clk x 2.4 GHz
 BF16_MATRIX_PEAK_TFLOPS = 2500.0    # dense bf16 / fp16 matrix cores
 INT8_MATRIX_PEAK_TOPS = 5000.0
+# fp32 operands as three bf16 parts: six bf16 products for one fp32 product
+PARTS_PEAK_TFLOPS = BF16_MATRIX_PEAK_TFLOPS / 6
 # Search times of the paper's nearest-neighbour table (Sec. 6.4), seconds:
 # one GPU of a GTX 295, and one core of a 2.4 GHz Core2 (C, gcc -O).
 PAPER_NN_GTX295_S = {4096: 0.089, 16384: 0.299, 65536: 1.146, 262144: 4.508, 1048576: 17.989}
@@ -127,9 +131,16 @@ def nn_fingerprint(plan) -> str:
 
 def batched_fingerprint(plan) -> str:
     """Hash of the batched plan's configuration (every variant) and the
-    igemm template its kernel is generated from (comments aside)."""
-    src = open(os.path.join(ROOT, "paper_0911_3456_amd", "csrc", "kernels", "igemm.hip")).read()
+    templates its kernel is generated from (comments aside)."""
+    src = "".join(open(os.path.join(ROOT, "paper_0911_3456_amd", "csrc", "kernels", f)).read()
+                  for f in ("igemm.hip", "rgemm.hip"))
     return hashlib.sha256((_code_only(src) + "\0" + plan.describe()).encode()).hexdigest()[:16]
+
+
+def fp32_peak(config: str) -> float:
+    """The bound of an fp32 role by its configuration: the fp32 matrix peak,
+    or for three-part operands the bf16 peak over six."""
+    return PARTS_PEAK_TFLOPS if "sp=1" in config or "algo=dws" in config else FP32_MATRIX_PEAK_TFLOPS
 
 
 TRAFFIC_FILES = {
@@ -316,17 +327,18 @@ def step_leg(name: str, steps: int, warmup: int, use_graph: bool = True, only: s
     dom = max(role_ms, key=role_ms.get)
     achieved = s.flops / (role_ms[dom] * 1e-3) / 1e12
     fp = kernel_fingerprint(plan, dom)
+    peak = {r: fp32_peak(plan.get_config(r)) for r in ROLES}
     out = {
         "shape": s, "plan_s": plan_s, "ms": sec * 1e3, "eager_ms": sec_eager * 1e3, "graph": graph_used,
         "gflops": flops / sec / 1e9,
         "kernels": {r: plan.get_config(r) for r in ROLES},
-        "roofline": {"bound": "mfma", "achieved": round(achieved, 3), "peak": FP32_MATRIX_PEAK_TFLOPS,
-                     "unit": "TFLOP/s", "frac": round(achieved / FP32_MATRIX_PEAK_TFLOPS, 4),
+        "roofline": {"bound": "mfma", "achieved": round(achieved, 3), "peak": round(peak[dom], 1),
+                     "unit": "TFLOP/s", "frac": round(achieved / peak[dom], 4),
                      "traffic": load_traffic(dom, fp, TRAFFIC_FILES[name]), "kernel": dom,
                      "kernel_ms": round(role_ms[dom], 5),
                      "per_role_ms": {r: round(v, 5) for r, v in role_ms.items()},
                      "per_role_tflops": {r: round(s.flops / (v * 1e-3) / 1e12, 3) for r, v in role_ms.items()},
-                     "per_role_frac": {r: round(s.flops / (v * 1e-3) / 1e12 / FP32_MATRIX_PEAK_TFLOPS, 4)
+                     "per_role_frac": {r: round(s.flops / (v * 1e-3) / 1e12 / peak[r], 4)
                                        for r, v in role_ms.items()},
                      "fingerprint": fp},
     }
@@ -445,8 +457,9 @@ def precision_leg(steps: int, warmup: int, use_graph: bool = True):
                                "traffic": load_traffic("forward", fp, TRAFFIC_FILES["precision_" + prec]),
                                "fingerprint": fp}
         elif algo == "igemm":
-            row["roofline"] = {"bound": "mfma", "achieved": row["tflops"], "peak": FP32_MATRIX_PEAK_TFLOPS,
-                               "unit": "TFLOP/s", "frac": round(row["tflops"] / FP32_MATRIX_PEAK_TFLOPS, 4)}
+            peak = fp32_peak(row["config"])
+            row["roofline"] = {"bound": "mfma", "achieved": row["tflops"], "peak": round(peak, 1),
+                               "unit": "TFLOP/s", "frac": round(row["tflops"] / peak, 4)}
         else:
             row["roofline"] = {"bound": "alu", "achieved": row["tflops"], "peak": FP32_VECTOR_PEAK_TFLOPS,
                                "unit": "TFLOP/s", "frac": round(row["tflops"] / FP32_VECTOR_PEAK_TFLOPS, 4)}
@@ -499,7 +512,7 @@ def batched_leg(steps: int, warmup: int):
         plan.enable_timing(False)
         k_ms, k_calls = plan.read_timing(reset=True)
         k_ms /= max(k_calls, 1)
-        # the whole launch replayed from the graph (counter reset + kernel)
+        # the whole launch replayed from the graph (packing + kernel)
         t0 = time.perf_counter()
         for _ in range(reps):
             plan.launch(use_graph=True)
@@ -514,8 +527,8 @@ def batched_leg(steps: int, warmup: int):
            "kernel_ms": round(k_ms, 3),
            "tflops": round(plan.flops / sec / 1e12, 2), "variants": nvar,
            "plan_s": round(plan_s, 2),
-           "roofline": {"bound": "mfma", "achieved": round(achieved, 3), "peak": FP32_MATRIX_PEAK_TFLOPS,
-                        "unit": "TFLOP/s", "frac": round(achieved / FP32_MATRIX_PEAK_TFLOPS, 4),
+           "roofline": {"bound": "mfma", "achieved": round(achieved, 3), "peak": round(fp32_peak(desc), 1),
+                        "unit": "TFLOP/s", "frac": round(achieved / fp32_peak(desc), 4),
                         "traffic": load_traffic("batched", fp, TRAFFIC_FILES["batched"]),
                         "kernel": "fbcorr_batched", "fingerprint": fp}}
     plan.close()

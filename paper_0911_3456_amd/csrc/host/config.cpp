@@ -1059,8 +1059,8 @@ Config heuristic_default(const fbcorr_desc& d, int role, const DeviceInfo& di) {
     std::string err;
     const Config plain = plain_default(d, role, di);
     if (h.algo == plain.algo || !build_role(d, role, h, di, rb, err)) return plain;
-    // A forward pass that the static scratch could serve stays one (the
-    // packed bank of fp32 filters is larger than the filters).
+    // A forward pass whose packed bank would outgrow the static scratch keeps
+    // fp32 instructions (parts are 6 bytes a weight; not timed at that size).
     RoleBuild pb;
     // Which filter gradients a plan takes does not hang on the choice of
     // kernel: one that algo=dw refuses for its size is refused here too.

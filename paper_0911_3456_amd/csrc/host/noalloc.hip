@@ -6,9 +6,9 @@
 // kernel's scalar-weight variant) taken from a file-scope device array
 // instead of a caller buffer, so that it calls no allocator at any point.  A
 // plan with the default fp32 configuration runs its kernel without scratch
-// (spare_forward): such calls may overlap.  Each device the library runs on holds its own copy of the array until the
-// process ends; its address on a device is looked up once, with that device
-// current, and kept.  In host code the array's name is only a stand-in for
+// (spare_forward): such calls may overlap.  Each device the library runs on
+// holds its own copy of the array until the process ends; its address on a
+// device is looked up once, with that device current, and kept.  In host code the array's name is only a stand-in for
 // the symbol: every use below goes through the looked-up device address.
 #include <hip/hip_runtime.h>
 

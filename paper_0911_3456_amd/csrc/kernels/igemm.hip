@@ -88,7 +88,7 @@ typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
 
 //@@BODY-BEGIN
 // Specialisation constants arrive as FB_<name> (see the host generator).
-// The image extents may instead be run-time values (the persistent batched
+// The image extents may instead be run-time values (the batched
 // kernel): then the body reads its hi_/wi_/ho_/wo_ arguments.
 #define FH FB_FH
 #define FW FB_FW
